@@ -37,9 +37,9 @@
  *    *status_d (int32, zeroed by the caller) and clamp.  Read it once per
  *    window.
  *  - Node ids are int32 in [0, num_nodes).  Feature rows are opaque bytes;
- *    row_bytes must be a multiple of 4 and at most 32768.  The 16-byte
- *    vector copy path is used when every base pointer and stride involved
- *    is a multiple of 16, a 4-byte path otherwise.
+ *    row_bytes must be a multiple of 4 and at most 32768.  Bases and strides
+ *    are multiples of 4; rows of 16 bytes and more move in 16-byte pieces
+ *    whatever their alignment, narrower ones in words.
  */
 #ifndef GG_H
 #define GG_H
@@ -168,9 +168,9 @@ typedef struct gg_tuning {
                                 default: as many as fit in 32 KB (staging) or 8 KB (gathers),
                                 a power of two except for a GG_GATHER_SHARED gather */
   int32_t gather_blocks;     /* blocks of one gather launch, shared by its segments,
-                                8..65536 (default 1024) */
+                                8..65536 (default 1024, or 512 with GG_GATHER_SHARED) */
   int32_t gather_loads;      /* 16-byte row loads in flight per lane in a gather: 2, 4 or 8
-                                (default 8, or 4 with GG_GATHER_SHARED) */
+                                (default 8) */
   int32_t stage_blocks;      /* most blocks of a staging copy, 1..65536 (default 16384) */
   int32_t stage_host_blocks; /* most blocks of a staging copy when a shard lives in host
                                 memory, 1..65536, or -1 for stage_blocks (default 128) */
@@ -396,9 +396,9 @@ int gg_stage_inplace(const int32_t* bucket_ids_d, const int64_t* owner_off_d, in
  * bounds_d = frontier_off + L*W and nseg = W it gathers the whole window.
  * No host synchronisation is needed.  Rows past n_cap are dropped and set
  * GG_DEV_CAPACITY.  flags: 0, or GG_GATHER_SHARED when other streams run
- * latency-bound work (sampling) on the device at the same time: each lane
- * then keeps half as many row loads in flight, which costs the gather a few
- * percent alone and leaves the memory system's queues short enough for the
+ * latency-bound work (sampling) on the device at the same time: the gather
+ * then runs in half as many blocks, which costs it a few percent alone and
+ * leaves room on the chip and in the memory system's queues for the
  * concurrent work, and a wavefront's tile of rows holds as many rows as fit
  * in 8 KB rather than a power of two.  Results are identical either way;
  * any other flag bit is GG_ERR_ARG. */

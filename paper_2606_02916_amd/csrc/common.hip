@@ -101,8 +101,8 @@ int resolve_tuning(const gg_tuning_t* t, Tune* out) {
   GG_REQUIRE(t->mark_min_batches >= -1 && t->mark_min_batches <= GG_MAX_W,
              "tuning: mark_min_batches %d outside 1..%d (or -1)", t->mark_min_batches, GG_MAX_W);
   out->tile_rows = t->tile_rows;
-  out->gather_blocks = t->gather_blocks ? t->gather_blocks : kGatherBlocksDefault;
-  out->gather_loads = t->gather_loads;
+  out->gather_blocks = t->gather_blocks;
+  out->gather_loads = t->gather_loads ? t->gather_loads : kGatherLoads;
   out->stage_blocks = t->stage_blocks ? t->stage_blocks : kStageBlocksDefault;
   out->stage_host_blocks = t->stage_host_blocks == 0 ? kStageHostBlocksDefault
                            : t->stage_host_blocks < 0 ? out->stage_blocks

@@ -1,5 +1,5 @@
 // Geometry of the row copy engine: how a tile of rows is cut into VB-byte
-// chunks (VB = 16 or 4) and how a chunk index maps back to its row.  Plain
+// chunks (VB = 16, or 4 for rows below 16 bytes) and how a chunk index maps back to its row.  Plain
 // integer code, shared by the host (which fills the struct) and the kernels
 // (which decode chunk indices); it needs no HIP header, so a host program
 // can check the map for every row width the library accepts.
@@ -21,6 +21,13 @@ struct CopyGeom {
   uint32_t magic;     // div_magic(cpr)
   uint32_t tail;      // 4-byte words after the full chunks (VB = 16 only)
   uint32_t tmagic;    // div_magic(tail)
+  // How the copy engine moves a row: `pieces` VB-byte pieces, piece p at byte
+  // min(p * VB, last).  A row that is not a multiple of 16 bytes ends in a
+  // piece that overlaps the one before (both write the same bytes there), so
+  // its last words need no pass of their own.
+  uint32_t pieces;
+  uint32_t pmagic;    // div_magic(pieces)
+  uint32_t last;      // row_bytes - VB
 };
 
 // Multiplier for c / d as the high word of c * magic: magic = ceil(2^32 / d).
@@ -46,6 +53,9 @@ inline CopyGeom copy_geom(int32_t row_bytes, int vb) {
   g.tail = vb == 16 ? (uint32_t)((row_bytes % 16) / 4) : 0u;
   g.magic = div_magic(g.cpr);
   g.tmagic = div_magic(g.tail);
+  g.pieces = g.cpr + (g.tail ? 1u : 0u);
+  g.pmagic = div_magic(g.pieces);
+  g.last = (uint32_t)(row_bytes > vb ? row_bytes - vb : 0);
   return g;
 }
 

@@ -26,10 +26,15 @@ namespace gg {
 namespace {
 
 constexpr int kTilesPerBlock = kBlock / kWave;  // 4 waves
-// Blocks per launch, shared by the segments (tuning gather_blocks): the
-// default 1024 (four per CU) beat 512, 768, 1536 and 2048 on a 1.5M-row
-// window, alone (236 us warm, 267 us cold) and beside the next window's
-// sampling.
+// Blocks per launch, shared by the segments (tuning gather_blocks).  Alone,
+// 1,024 (four per CU): whole sequential windows took 474 / 325 us (1.5M rows
+// of 400 bytes with misses / 211K unaligned rows of 2,408) against 548 / 335
+// with 512, 492 / 326 with 768 and 492 / 342 with 1,536.  Beside the next
+// window's sampling and staging, 512: eight loads per lane keep enough bytes
+// in flight with half the blocks, and the rest of the chip goes to the other
+// chain (six look-ahead windows of 1.5M 400-byte rows / 295K 2,408-byte rows:
+// 2,135 / 2,018 us, against 2,300 / 2,205 with 1,024, 2,205 / 2,117 with 768,
+// 2,204 / 2,018 with 448 and 2,221 / 1,987 with 512 and four loads).
 
 struct GatherArgs {
   int64_t n_cap;        // output rows available
@@ -249,12 +254,16 @@ struct GatherWs {
   int32_t* blk_stat;   // per row block: local, hits, misses per owner
 };
 
-int32_t blocks_per_seg(int64_t n_cap, int32_t nseg, const Tune& tune) {
-  int64_t bx = std::max<int64_t>(tune.gather_blocks / nseg, 8);
+int32_t blocks_per_seg(int64_t n_cap, int32_t nseg, const Tune& tune, bool shared = false) {
+  const int32_t blocks = tune.gather_blocks ? tune.gather_blocks
+                         : shared           ? kGatherBlocksShared
+                                            : kGatherBlocksAlone;
+  int64_t bx = std::max<int64_t>(blocks / nseg, 8);
   bx = std::min<int64_t>(bx, std::max<int64_t>(1, cdiv(n_cap, kBlock)));
   return (int32_t)bx;
 }
 
+// Sized for a gather alone, which launches at least as many blocks as a shared one.
 size_t gather_ws_layout(int64_t n_cap, int32_t nseg, int32_t P, const Tune& tune, char* base,
                         GatherWs* out) {
   const int64_t bx = blocks_per_seg(n_cap, nseg, tune);
@@ -389,10 +398,7 @@ int gather_impl(const int32_t* in_ids_d, const int64_t* bounds_d, int32_t nseg, 
   GG_REQUIRE(ws && ws_bytes >= need_ws, "workspace of %zu bytes < %zu", ws_bytes, need_ws);
   GatherWs gw;
   gather_ws_layout(n_cap, nseg, kp.P, tune, (char*)ws, &gw);
-  bool v16 = aligned16(out_d) && out_stride % 16 == 0 &&
-             (cache_rows == 0 || (aligned16(cache_d) && cache_stride % 16 == 0));
-  for (int m = 0; m < kf.P; ++m)
-    if (kf.rows[m] > 0) v16 = v16 && aligned16(kf.shard[m]) && kf.stride[m] % 16 == 0;
+  const bool v16 = copy_by_16(kf.row_bytes);
   GatherArgs a;
   a.n_cap = n_cap;
   a.cache_stride = cache_stride;
@@ -400,33 +406,25 @@ int gather_impl(const int32_t* in_ids_d, const int64_t* bounds_d, int32_t nseg, 
   a.out_stride = out_stride;
   a.nseg = nseg;
   a.nstat = 2 + kp.P;
-  // Tiles of up to 8 KB.  Against 32 KB tiles the isolated gather took 228
-  // instead of 237 us on a 1.5M-row window of 400-byte rows and 246 instead
-  // of 261 us on 275K rows of 2,408 bytes: more, smaller tiles leave a
-  // shorter tail of waves still copying their last tile.  With four loads
-  // in flight (shared) a tile holds as many rows as fit, 20 of 400 bytes
-  // (500 chunks: two steps of 256 loads, 98% full), which took the isolated
-  // gather from 0.58 to 0.60 of HBM peak on that window and from 0.55 to
-  // 0.57 on the wide rows; with eight (alone) it stays a power of two, 16
-  // rows and 2, which measured 1-3% faster there than 20 and 3.
+  // Tiles of up to 8 KB: more, smaller tiles leave a shorter tail of waves
+  // still copying their last tile than 32 KB ones (400-byte rows 228 against
+  // 237 us alone, 2,408-byte rows 246 against 261).  Shared, a tile holds as
+  // many rows as fit, 20 of 400 bytes (500 pieces of a step's 512); alone it
+  // stays a power of two, 16 rows and 2, which measured 1-3% faster there
+  // than 20 and 3.
   const bool shared = (flags & GG_GATHER_SHARED) != 0;
   a.tile = copy_tile(tune, kf.row_bytes, 8192, !shared);
   a.pad_ = 0;
   a.geom = copy_geom(kf.row_bytes, v16 ? 16 : 4);
-  const int32_t bx = blocks_per_seg(n_cap, nseg, tune);
-  // Row loads in flight per lane: eight alone; four when sharing the chip
-  // (with eight, a concurrent sampler ran ~15% slower and the look-ahead
-  // window took 6% longer, for 4% more gather speed).
-  const int unroll = tune.gather_loads ? tune.gather_loads
-                                       : (shared ? kGatherLoadsShared : kGatherLoadsAlone);
+  const int32_t bx = blocks_per_seg(n_cap, nseg, tune, shared);
   const char* cache = (const char*)cache_d;
   char* out = (char*)out_d;
   // Output rows are stored non-temporally: the gather never reads them back.
   if (v16)
-    launch_gather<16, true>(stream, unroll, bx, in_ids_d, bounds_d, kp, kf, a, cache, slot_of_d,
+    launch_gather<16, true>(stream, tune.gather_loads, bx, in_ids_d, bounds_d, kp, kf, a, cache, slot_of_d,
                             out, gw, stats_d, status_d);
   else
-    launch_gather<4, true>(stream, unroll, bx, in_ids_d, bounds_d, kp, kf, a, cache, slot_of_d,
+    launch_gather<4, true>(stream, tune.gather_loads, bx, in_ids_d, bounds_d, kp, kf, a, cache, slot_of_d,
                            out, gw, stats_d, status_d);
   GG_LAUNCH_CHECK("k_gather_rows/k_gather_finish");
   return GG_OK;

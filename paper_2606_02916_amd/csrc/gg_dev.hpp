@@ -194,89 +194,90 @@ __device__ __forceinline__ void wave_hist_add(int32_t* hist, bool valid, int32_t
 // ---------------------------------------------------------------------------
 // Row copy engine.  A wavefront copies up to 64 rows: lane r supplies the
 // source of row r (nullptr = skip that row) and the rows land at
-// dst0 + r * dst_stride.  The row bytes are cut into VB-byte chunks that are
-// spread over the wave, so consecutive lanes move consecutive chunks of one
+// dst0 + r * dst_stride.  The row bytes are cut into VB-byte pieces that are
+// spread over the wave, so consecutive lanes move consecutive pieces of one
 // row and then of the next: every load and store instruction covers a
 // contiguous run of up to 1 KB, and short rows do not leave lanes idle.
-// Chunk c belongs to row c / cpr, computed by chunk_row (copy_geom.hpp).
+// Piece c belongs to row c / pieces, computed by chunk_row (copy_geom.hpp).
+// VB is 16 for rows of 16 bytes and more, at whatever multiple of 4 the rows
+// start (global_load/store_dwordx4 need dword alignment only), and 4 for
+// narrower rows.  Bound by memory.  Moving unaligned rows in words held four
+// times as many instructions per byte: windows of 211K unpadded 2,408-byte
+// rows took 592 us and now take 322, of 8 launches of 23K 300-byte rows 578
+// and now 323 (whole sequential windows).
 // ---------------------------------------------------------------------------
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 __attribute__((aligned(4))) u32x4_a4;   // at any multiple of 4
 
-template <bool NT>
-__device__ __forceinline__ void st16(char* p, u32x4 v) {
-  if (NT)
-    __builtin_nontemporal_store(v, (u32x4*)p);
-  else
-    *(u32x4*)p = v;
+template <int VB>
+struct Piece;
+template <>
+struct Piece<16> {
+  typedef u32x4 val;
+  typedef u32x4_a4 mem;
+};
+template <>
+struct Piece<4> {
+  typedef uint32_t val;
+  typedef uint32_t mem;
+};
+
+// Row addresses come out of shuffles as integers, so the compiler can't tell
+// that they are global memory and would issue flat accesses, whose results
+// the wave counts together with its LDS operations: every shuffle's wait
+// would then also wait for the loads in flight.
+#define GG_GLOBAL __attribute__((address_space(1)))
+
+template <int VB>
+__device__ __forceinline__ typename Piece<VB>::val ld_piece(const char* p) {
+  typedef typename Piece<VB>::mem mem;
+  return *(const GG_GLOBAL mem*)p;
 }
 
-template <bool NT>
-__device__ __forceinline__ void st4(char* p, uint32_t v) {
+template <int VB, bool NT>
+__device__ __forceinline__ void st_piece(char* p, typename Piece<VB>::val v) {
+  typedef typename Piece<VB>::mem mem;
   if (NT)
-    __builtin_nontemporal_store(v, (uint32_t*)p);
+    __builtin_nontemporal_store(v, (GG_GLOBAL mem*)p);
   else
-    *(uint32_t*)p = v;
+    *(GG_GLOBAL mem*)p = v;
+}
+
+// Row and byte of piece c.
+__device__ __forceinline__ uint32_t piece_at(const CopyGeom& g, uint32_t c, int vb,
+                                             uint32_t* row) {
+  const uint32_t r = chunk_row(c, g.pmagic);
+  const uint32_t off = (c - r * g.pieces) * (uint32_t)vb;
+  *row = r;
+  return off < g.last ? off : g.last;
 }
 
 template <int VB, bool NT, int U = (VB == 16 ? 4 : 8)>
 __device__ __forceinline__ void wave_copy_rows(const char* src, char* dst0, int64_t dst_stride,
                                                int nrows, const CopyGeom& g) {
   const int lane = lane_id();
-  const uint32_t total = (uint32_t)nrows * g.cpr;
+  const uint32_t total = (uint32_t)nrows * g.pieces;
   const long long srcl = (long long)src;
   for (uint32_t base = 0; base < total; base += kWave * U) {
-    if (VB == 16) {
-      // Destinations are recomputed at the stores: holding U 64-bit
-      // pointers across the loads would cost 2U registers.
-      u32x4 v[U];
-      bool ok[U];
+    // Destinations are recomputed at the stores: holding U 64-bit pointers
+    // across the loads would cost 2U registers.
+    typename Piece<VB>::val v[U];
+    bool ok[U];
 #pragma unroll
-      for (int j = 0; j < U; ++j) {
-        const uint32_t c = base + (uint32_t)(j * kWave + lane);
-        const uint32_t r = chunk_row(c, g.magic);
-        const uint32_t col = c - r * g.cpr;
-        const char* sp = (const char*)__shfl(srcl, (int)(r & 63u), kWave);
-        ok[j] = (c < total) && (sp != nullptr);
-        if (ok[j]) v[j] = *(const u32x4*)(sp + (int64_t)col * 16);
-      }
-#pragma unroll
-      for (int j = 0; j < U; ++j) {
-        const uint32_t c = base + (uint32_t)(j * kWave + lane);
-        const uint32_t r = chunk_row(c, g.magic);
-        const uint32_t col = c - r * g.cpr;
-        if (ok[j]) st16<NT>(dst0 + (int64_t)r * dst_stride + (int64_t)col * 16, v[j]);
-      }
-    } else {
-      uint32_t v[U];
-      char* dp[U];
-      bool ok[U];
-#pragma unroll
-      for (int j = 0; j < U; ++j) {
-        const uint32_t c = base + (uint32_t)(j * kWave + lane);
-        const uint32_t r = chunk_row(c, g.magic);
-        const uint32_t col = c - r * g.cpr;
-        const char* sp = (const char*)__shfl(srcl, (int)(r & 63u), kWave);
-        ok[j] = (c < total) && (sp != nullptr);
-        dp[j] = dst0 + (int64_t)r * dst_stride + (int64_t)col * 4;
-        if (ok[j]) v[j] = *(const uint32_t*)(sp + (int64_t)col * 4);
-      }
-#pragma unroll
-      for (int j = 0; j < U; ++j)
-        if (ok[j]) st4<NT>(dp[j], v[j]);
-    }
-  }
-  if (VB == 16 && g.tail) {
-    const uint32_t ttotal = (uint32_t)nrows * g.tail;
-    const int64_t off0 = (int64_t)g.cpr * 16;
-    for (uint32_t base = 0; base < ttotal; base += kWave) {
-      const uint32_t c = base + (uint32_t)lane;
-      const uint32_t r = chunk_row(c, g.tmagic);
-      const uint32_t w = c - r * g.tail;
+    for (int j = 0; j < U; ++j) {
+      const uint32_t c = base + (uint32_t)(j * kWave + lane);
+      uint32_t r;
+      const uint32_t off = piece_at(g, c, VB, &r);
       const char* sp = (const char*)__shfl(srcl, (int)(r & 63u), kWave);
-      if (c < ttotal && sp != nullptr) {
-        const uint32_t v = *(const uint32_t*)(sp + off0 + (int64_t)w * 4);
-        st4<NT>(dst0 + (int64_t)r * dst_stride + off0 + (int64_t)w * 4, v);
-      }
+      ok[j] = (c < total) && (sp != nullptr);
+      if (ok[j]) v[j] = ld_piece<VB>(sp + off);
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const uint32_t c = base + (uint32_t)(j * kWave + lane);
+      uint32_t r;
+      const uint32_t off = piece_at(g, c, VB, &r);
+      if (ok[j]) st_piece<VB, NT>(dst0 + (int64_t)r * dst_stride + off, v[j]);
     }
   }
 }
@@ -287,59 +288,25 @@ template <int VB, bool NT, int U = (VB == 16 ? 4 : 8)>
 __device__ __forceinline__ void wave_copy_rows_to(const char* src, char* dst, int nrows,
                                                   const CopyGeom& g) {
   const int lane = lane_id();
-  const uint32_t total = (uint32_t)nrows * g.cpr;
+  const uint32_t total = (uint32_t)nrows * g.pieces;
   const long long srcl = (long long)src, dstl = (long long)dst;
   for (uint32_t base = 0; base < total; base += kWave * U) {
-    if (VB == 16) {
-      u32x4 v[U];
-      char* dp[U];
-      bool ok[U];
+    typename Piece<VB>::val v[U];
+    char* dp[U];
+    bool ok[U];
 #pragma unroll
-      for (int j = 0; j < U; ++j) {
-        const uint32_t c = base + (uint32_t)(j * kWave + lane);
-        const uint32_t r = chunk_row(c, g.magic);
-        const uint32_t col = c - r * g.cpr;
-        const char* sp = (const char*)__shfl(srcl, (int)(r & 63u), kWave);
-        dp[j] = (char*)__shfl(dstl, (int)(r & 63u), kWave) + (int64_t)col * 16;
-        ok[j] = (c < total) && (sp != nullptr);
-        if (ok[j]) v[j] = *(const u32x4*)(sp + (int64_t)col * 16);
-      }
-#pragma unroll
-      for (int j = 0; j < U; ++j)
-        if (ok[j]) st16<NT>(dp[j], v[j]);
-    } else {
-      uint32_t v[U];
-      char* dp[U];
-      bool ok[U];
-#pragma unroll
-      for (int j = 0; j < U; ++j) {
-        const uint32_t c = base + (uint32_t)(j * kWave + lane);
-        const uint32_t r = chunk_row(c, g.magic);
-        const uint32_t col = c - r * g.cpr;
-        const char* sp = (const char*)__shfl(srcl, (int)(r & 63u), kWave);
-        dp[j] = (char*)__shfl(dstl, (int)(r & 63u), kWave) + (int64_t)col * 4;
-        ok[j] = (c < total) && (sp != nullptr);
-        if (ok[j]) v[j] = *(const uint32_t*)(sp + (int64_t)col * 4);
-      }
-#pragma unroll
-      for (int j = 0; j < U; ++j)
-        if (ok[j]) st4<NT>(dp[j], v[j]);
-    }
-  }
-  if (VB == 16 && g.tail) {
-    const uint32_t ttotal = (uint32_t)nrows * g.tail;
-    const int64_t off0 = (int64_t)g.cpr * 16;
-    for (uint32_t base = 0; base < ttotal; base += kWave) {
-      const uint32_t c = base + (uint32_t)lane;
-      const uint32_t r = chunk_row(c, g.tmagic);
-      const uint32_t w = c - r * g.tail;
+    for (int j = 0; j < U; ++j) {
+      const uint32_t c = base + (uint32_t)(j * kWave + lane);
+      uint32_t r;
+      const uint32_t off = piece_at(g, c, VB, &r);
       const char* sp = (const char*)__shfl(srcl, (int)(r & 63u), kWave);
-      char* dp = (char*)__shfl(dstl, (int)(r & 63u), kWave);
-      if (c < ttotal && sp != nullptr) {
-        const uint32_t v = *(const uint32_t*)(sp + off0 + (int64_t)w * 4);
-        st4<NT>(dp + off0 + (int64_t)w * 4, v);
-      }
+      dp[j] = (char*)__shfl(dstl, (int)(r & 63u), kWave) + off;
+      ok[j] = (c < total) && (sp != nullptr);
+      if (ok[j]) v[j] = ld_piece<VB>(sp + off);
     }
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+      if (ok[j]) st_piece<VB, NT>(dp[j], v[j]);
   }
 }
 

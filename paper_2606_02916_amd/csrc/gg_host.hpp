@@ -62,9 +62,9 @@ inline int32_t fill_rows(int32_t row_bytes, int32_t max_bytes) {
 }
 
 // Launch-shape defaults (gg_tuning_t fields left 0).
-constexpr int kGatherBlocksDefault = 1024;   // gather blocks per launch
-constexpr int kGatherLoadsAlone = 8;         // row loads in flight per lane
-constexpr int kGatherLoadsShared = 4;        // ... under GG_GATHER_SHARED
+constexpr int kGatherBlocksAlone = 1024;     // gather blocks per launch
+constexpr int kGatherBlocksShared = 512;     // ... under GG_GATHER_SHARED
+constexpr int kGatherLoads = 8;              // row loads in flight per lane
 constexpr int kStageBlocksDefault = 16384;   // most staging blocks (device shards)
 constexpr int kStageHostBlocksDefault = 128; // ... when a shard is in host memory
 constexpr int kEmitBlocksMax = 512;          // most in-place free-list blocks
@@ -77,8 +77,8 @@ constexpr int kMarkBlockLanes = 256;         // lanes per mark block
 // gg_tuning_t checked and resolved against the defaults.
 struct Tune {
   int32_t tile_rows;          // 0: by row width
-  int32_t gather_blocks;
-  int32_t gather_loads;       // 0: by GG_GATHER_SHARED
+  int32_t gather_blocks;      // 0: by GG_GATHER_SHARED
+  int32_t gather_loads;
   int32_t stage_blocks;
   int32_t stage_host_blocks;
   int32_t emit_blocks;
@@ -101,6 +101,11 @@ int resolve_tuning(const gg_tuning_t* t, Tune* out);
 // or the tuning's tile_rows when set (1 makes a wavefront copy one row per
 // step).
 int32_t copy_tile(const Tune& tune, int32_t row_bytes, int32_t max_bytes, bool pow2 = true);
+
+// Rows of 16 bytes and more move in 16-byte pieces whatever their alignment
+// (every base and stride is a multiple of 4, which is all the hardware's
+// 16-byte accesses need); narrower rows in words.
+inline bool copy_by_16(int32_t row_bytes) { return row_bytes >= 16; }
 
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 

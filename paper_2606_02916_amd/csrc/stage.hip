@@ -638,10 +638,7 @@ extern "C" int gg_stage_bulk(const int32_t* bucket_ids_d, const int64_t* owner_o
   if (rc != GG_OK) return rc;
   GG_REQUIRE(cache_stride >= kf.row_bytes && cache_stride % 4 == 0, "cache_stride %lld invalid",
              (long long)cache_stride);
-  bool v16 = aligned16(cache_d) && cache_stride % 16 == 0 &&
-             (src_cache_d == nullptr || aligned16(src_cache_d));
-  for (int m = 0; m < kf.P; ++m)
-    if (kf.rows[m] > 0) v16 = v16 && aligned16(kf.shard[m]) && kf.stride[m] % 16 == 0;
+  const bool v16 = copy_by_16(kf.row_bytes);
   StageArgs a;
   a.cap = cap;
   a.cache_rows = cache_rows;
@@ -731,9 +728,7 @@ extern "C" int gg_stage_inplace(const int32_t* bucket_ids_d, const int64_t* owne
   InplaceWs w;
   const size_t need_ws = inplace_ws_layout(cap, cache_rows, kp.P, (char*)ws, &w);
   GG_REQUIRE(ws && ws_bytes >= need_ws, "workspace of %zu bytes < %zu", ws_bytes, need_ws);
-  bool v16 = aligned16(cache_d) && cache_stride % 16 == 0;
-  for (int m = 0; m < kf.P; ++m)
-    if (kf.rows[m] > 0) v16 = v16 && aligned16(kf.shard[m]) && kf.stride[m] % 16 == 0;
+  const bool v16 = copy_by_16(kf.row_bytes);
   StageArgs a;
   a.cap = cap;
   a.cache_rows = cache_rows;

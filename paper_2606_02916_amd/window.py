@@ -314,7 +314,7 @@ class FetchPipeline:
         """All Wk batches of the window in one launch; batch b's rows start at
         row frontier_off[L*Wk + b] - frontier_off[L*Wk] of out.  flags:
         gg_gather_batch's (GG_GATHER_SHARED: the look-ahead's tiles and
-        loads in flight)."""
+        blocks)."""
         out = self.win_out if out is None else out
         bounds = self.frontier_off.data_ptr() + 8 * (self.L * Wk)
         gg.gg_gather_batch(self.frontier_ids, bounds, Wk, out.shape[0], self.part, self.feat,
