@@ -470,6 +470,9 @@ class LookaheadPipeline:
         self.cache_stride = int(cache_stride) if cache_stride else self.stride
         self.n_hot = int(n_hot)
         self.hot_frac = hot_frac
+        # The CSR struct holds addresses only: the tensors live as long as the
+        # pipeline, as FetchPipeline's do.
+        self.row_ptr, self.col_idx = row_ptr, col_idx
         self.csr = gg.make_csr(row_ptr, col_idx)
         self.part = gg.make_part(self.P, part_kind, local_owner, self.N, range_start)
         self.feat = gg.make_feat(self.row_bytes, shards, [self.stride] * self.P, shard_rows)
