@@ -4,14 +4,14 @@
 // Grid (bx, nseg): blocks (., s) serve segment (batch) s, so every block's
 // statistics belong to one batch and reduce without atomics.  Each
 // wavefront takes a tile of consecutive output rows at a time (up to 64
-// rows and 8 KB); every lane of the tile resolves
-// its row (local shard, cache slot, or miss) and the wave copies the
-// resolved rows with the row copy engine.  Misses are only counted, per
-// block and owner.  A second launch serves them: one block per row block
-// of the first launch, which returns at once when that block counted no
-// miss and otherwise walks the same tiles again and copies the missed rows
-// from their owners' shards straight into their output rows.  No queue and
-// no counter need clearing between calls.
+// rows and 8 KB); every lane of the tile resolves its row (local shard,
+// cache slot, or the owner's shard for a miss) and the wave copies the
+// resolved rows with the row copy engine.  Misses differ only in where the
+// row comes from and in the counts per block and owner; a pass of their own
+// over the same tiles would resolve every row again (a sequential window of
+// 1.5M rows, two thirds of its remote ones misses: 480 us with two passes, 439
+// with one).  A second launch of one block per segment sums the blocks'
+// statistics.
 #include <stdlib.h>
 #include <string.h>
 
@@ -132,6 +132,11 @@ __global__ void __launch_bounds__(kBlock) k_gather_rows(const int32_t* in_ids, c
       } else {
         if (cur.s >= 0) st |= GG_DEV_BAD_ROW;
         miss = true;
+        const int64_t r = row_of(part, s_start, cur.u, cur.m);
+        if (r < feat.rows[cur.m])
+          src = feat.shard[cur.m] + r * feat.stride[cur.m];   // on demand, from the owner
+        else
+          st |= GG_DEV_BAD_ROW;
       }
     }
     const uint64_t ml = __ballot(is_local), mh = __ballot(is_hit), mm = __ballot(miss);
@@ -162,92 +167,42 @@ __global__ void __launch_bounds__(kBlock) k_gather_rows(const int32_t* in_ids, c
   for (int t = threadIdx.x; t < a.nstat; t += blockDim.x) dst[t] = s_cnt[t];
 }
 
-// Blocks 0 .. nseg-1: statistics of batch s.  Block nseg + s * bx + x
-// serves the misses of row block (x, s) of k_gather_rows, if it had any.
-template <int VB, bool NT>
-__global__ void __launch_bounds__(kBlock) k_gather_finish(const int32_t* in_ids, const int64_t* bounds,
-                                                          KPart part, KFeat feat, GatherArgs a,
-                                                          int32_t bx, const int32_t* blk_stat,
-                                                          const int32_t* slot_of, char* out,
-                                                          gg_gather_stats_t* stats,
-                                                          int32_t* status) {
-  const int P = part.P;
-  if ((int)blockIdx.x < a.nseg) {
-    __shared__ int32_t s_sum[2 + GG_MAX_PARTS];
-    const int s = blockIdx.x;
-    for (int t = threadIdx.x; t < 2 + GG_MAX_PARTS; t += blockDim.x) s_sum[t] = 0;
-    __syncthreads();
-    for (int j = 0; j < a.nstat; ++j) {
-      int32_t v = 0;
-      for (int x = threadIdx.x; x < bx; x += blockDim.x) v += blk_stat[((int64_t)s * bx + x) * a.nstat + j];
-      v = wave_sum(v);
-      if (lane_id() == 0 && v) atomicAdd(&s_sum[j], v);
-    }
-    __syncthreads();
-    gg_gather_stats_t* o = stats + s;
-    if (threadIdx.x < GG_MAX_PARTS) {
-      const int m = threadIdx.x;
-      const int64_t rows = m < P ? (int64_t)s_sum[2 + m] : 0;
-      o->miss_rows[m] = rows;
-      o->miss_requests[m] = rows > 0 ? 1 : 0;
-    }
-    if (threadIdx.x == 0) {
-      int64_t misses = 0;
-      for (int m = 0; m < P; ++m) misses += s_sum[2 + m];
-      int64_t lo, hi;
-      seg_range(bounds, s, a, &lo, &hi);
-      o->rows = hi - lo;
-      o->local = s_sum[0];
-      o->hits = s_sum[1];
-      o->misses = misses;
-      if (bounds[s + 1] - bounds[0] > a.n_cap) set_status(status, GG_DEV_CAPACITY);
-    }
-    return;
-  }
-  const int64_t rb = blockIdx.x - a.nseg;    // row block (x, seg) of k_gather_rows
-  const int seg = (int)(rb / bx), x = (int)(rb % bx);
-  const int32_t* bs = blk_stat + rb * a.nstat;
-  int32_t nmiss = 0;
-  for (int m = 0; m < P; ++m) nmiss += bs[2 + m];
-  if (nmiss == 0) return;
-  __shared__ int64_t s_start[GG_MAX_PARTS + 1];
-  for (int t = threadIdx.x; t <= GG_MAX_PARTS; t += blockDim.x) s_start[t] = part.start[t];
+// Block s: the statistics of batch s from its blocks' counts.
+__global__ void __launch_bounds__(kBlock) k_gather_stats(const int64_t* bounds, int32_t P,
+                                                         GatherArgs a, int32_t bx,
+                                                         const int32_t* blk_stat,
+                                                         gg_gather_stats_t* stats,
+                                                         int32_t* status) {
+  __shared__ int32_t s_sum[2 + GG_MAX_PARTS];
+  const int s = blockIdx.x;
+  for (int t = threadIdx.x; t < 2 + GG_MAX_PARTS; t += blockDim.x) s_sum[t] = 0;
   __syncthreads();
-  int64_t lo, hi;
-  seg_range(bounds, seg, a, &lo, &hi);
-  const int64_t begin = bounds[0];
-  const int lane = lane_id();
-  const int64_t ntiles = (hi - lo + a.tile - 1) / a.tile;
-  int32_t st = 0;
-  // The tiles k_gather_rows gave this row block, in the same order.
-  for (int64_t t = (int64_t)x * kTilesPerBlock + threadIdx.x / kWave; t < ntiles;
-       t += (int64_t)bx * kTilesPerBlock) {
-    const int64_t r0 = lo + t * a.tile;
-    const int64_t i = r0 + lane;
-    const char* src = nullptr;
-    if (lane < a.tile && i < hi) {
-      const int32_t u = in_ids[begin + i];
-      if (u >= 0 && (int64_t)u < part.N) {
-        const int32_t m = owner_of(part, s_start, u);
-        if (m != part.local) {
-          const int32_t sl = slot_of[u];
-          if (!(sl >= 0 && (int64_t)sl < a.cache_rows)) {
-            const int64_t r = row_of(part, s_start, u, m);
-            if (r < feat.rows[m])
-              src = feat.shard[m] + r * feat.stride[m];
-            else
-              st |= GG_DEV_BAD_ROW;
-          }
-        }
-      }
-    }
-    if (__ballot(src != nullptr)) {
-      const int64_t left = hi - r0;
-      wave_copy_rows<VB, NT>(src, out + r0 * a.out_stride, a.out_stride,
-                             left < a.tile ? (int)left : a.tile, a.geom);
-    }
+  for (int j = 0; j < a.nstat; ++j) {
+    int32_t v = 0;
+    for (int x = threadIdx.x; x < bx; x += blockDim.x)
+      v += blk_stat[((int64_t)s * bx + x) * a.nstat + j];
+    v = wave_sum(v);
+    if (lane_id() == 0 && v) atomicAdd(&s_sum[j], v);
   }
-  if (st) set_status(status, st);
+  __syncthreads();
+  gg_gather_stats_t* o = stats + s;
+  if (threadIdx.x < GG_MAX_PARTS) {
+    const int m = threadIdx.x;
+    const int64_t rows = m < P ? (int64_t)s_sum[2 + m] : 0;
+    o->miss_rows[m] = rows;
+    o->miss_requests[m] = rows > 0 ? 1 : 0;
+  }
+  if (threadIdx.x == 0) {
+    int64_t misses = 0;
+    for (int m = 0; m < P; ++m) misses += s_sum[2 + m];
+    int64_t lo, hi;
+    seg_range(bounds, s, a, &lo, &hi);
+    o->rows = hi - lo;
+    o->local = s_sum[0];
+    o->hits = s_sum[1];
+    o->misses = misses;
+    if (bounds[s + 1] - bounds[0] > a.n_cap) set_status(status, GG_DEV_CAPACITY);
+  }
 }
 
 struct GatherWs {
@@ -291,8 +246,8 @@ void launch_gather(hipStream_t stream, int unroll, int32_t bx, const int32_t* in
   else
     hipLaunchKernelGGL((k_gather_rows<VB, NT, VB == 16 ? 4 : 8>), dim3(bx, a.nseg), dim3(kBlock), 0,
                        stream, in_ids, bounds, kp, kf, a, cache, slot_of, out, w.blk_stat, status);
-  hipLaunchKernelGGL((k_gather_finish<VB, NT>), dim3(a.nseg + a.nseg * bx), dim3(kBlock), 0, stream,
-                     in_ids, bounds, kp, kf, a, bx, w.blk_stat, slot_of, out, stats, status);
+  hipLaunchKernelGGL(k_gather_stats, dim3(a.nseg), dim3(kBlock), 0, stream, bounds, kp.P, a, bx,
+                     w.blk_stat, stats, status);
 }
 
 }  // namespace
@@ -426,7 +381,7 @@ int gather_impl(const int32_t* in_ids_d, const int64_t* bounds_d, int32_t nseg, 
   else
     launch_gather<4, true>(stream, tune.gather_loads, bx, in_ids_d, bounds_d, kp, kf, a, cache, slot_of_d,
                            out, gw, stats_d, status_d);
-  GG_LAUNCH_CHECK("k_gather_rows/k_gather_finish");
+  GG_LAUNCH_CHECK("k_gather_rows/k_gather_stats");
   return GG_OK;
 }
 
