@@ -526,14 +526,16 @@ size_t gg_ws_sage(int64_t num_nodes, int32_t W, int64_t rows_cap, int32_t L,
  * S(v) being v's neighbours drawn at hop L-j; h^0 = x_d, the rows of the
  * window's N_b back to back as gg_gather_batch writes them for the whole
  * window (layers_h[0].d_in elements of x_dtype per row at x_stride bytes;
- * at least min(rows_cap, |N_b| summed over the window) rows).  The first
- * layer finds rows of N_b by rank in smp->frontier_bits, which must still
- * hold the window's N_b (num_nodes is the graph's node count).
+ * at least min(rows_cap, |N_b| summed over the window) rows).  Rows are
+ * found by rank in smp->frontier_bits, which must still hold the window's
+ * N_b, as must the lists of every level (num_nodes is the graph's node
+ * count).
  * out_d receives the rows of F_0 (each batch's distinct seeds) of all
  * batches back to back, layers_h[L-1].d_out fp32 per row; out_rows_cap
- * bounds them.  The dense products run on MFMA in fp32 (each layer first
- * projects its input by [W_self | W_neigh], then averages the projected
- * neighbour rows: the same linear map in the other order).  A level with
+ * bounds them.  The dense products run on MFMA in fp32 (a layer averages
+ * its neighbour rows and multiplies, or projects its input by [W_self |
+ * W_neigh] and averages the projected rows: the same linear map in the other
+ * order, whichever moves less).  A level with
  * more rows than rows_cap, or seeds beyond out_rows_cap, set
  * GG_DEV_CAPACITY and the excess is skipped. */
 int gg_sage_forward(const gg_wsample_t* smp, int64_t num_nodes, int32_t W, int32_t L,

@@ -1,21 +1,27 @@
 // The consumer of X_b: GraphSAGE layers with the mean aggregator over the
-// sampled blocks of a window (Algorithm 1 forward pass; Sec. VI-A model).
+// sampled blocks of a window (Algorithm 1 forward pass; Sec. VI-A model), all
+// W batches of the window at once.
 //
-// Each layer runs as two launches over all W batches at once:
-//  * k_sage_project: Z = H [W_self | W_neigh] for every input row, a dense
-//    fp32 product on MFMA (v_mfma_f32_16x16x4f32).  Each wave owns 16 rows
-//    and loads them straight into registers, 16 bytes per lane; the weights
-//    sit in LDS;
-//  * k_sage_aggregate: out_v = act(Z_self[v] + mean_{u in S(v)} Z_neigh[u] +
-//    bias).  The mean commutes with the linear map, so averaging the
-//    projected rows (d_out wide) equals projecting the averaged input rows
-//    (d_in wide) up to rounding, and reads 64-byte rows instead of d_in-wide
-//    ones.
-// A node's row in the input level is its position in that level's ascending
-// frontier.  For the first layer (input level N_b) the position is a rank in
-// the batch's N_b bit set: a prefix count per word (k_rank_local,
-// k_rank_chunks) plus a popcount.  Deeper layers binary-search the (small)
-// frontier.  Nothing of size N per level is needed.
+// Three launches prepare a call: the ranks in the N_b bit sets and the weights
+// in matrix-core order (k_sage_prepare), each node's place in its own level (k_sage_places), and
+// for every output node the input rows of itself and of its neighbours
+// (k_sage_rows, every level in one launch).  Random lookups run there, with
+// one thread each, and not in front of the row reads.  Then each layer,
+// out_v = act(W_self^T h_v + W_neigh^T mean_{u in S(v)} h_u + bias), takes one
+// of two forms (use_projection says which):
+//  * k_sage_layer: a wave builds [h_v | mean h_u] of 16 output nodes in the
+//    registers that the fp32 MFMA reads (v_mfma_f32_16x16x4f32), a few column
+//    groups at a time, and multiplies them by the weights in LDS.  Nothing is
+//    projected that no output needs, and no projected row goes through memory;
+//  * k_sage_project and k_sage_mean: Z = H [W_self | W_neigh] for every input
+//    row, then the mean of projected rows, which commutes with the linear
+//    map: where rows are wide and outputs narrow, each input row is read once
+//    and the random reads are of 128-byte rows.
+//
+// A node's row in level N_b is its rank in the batch's N_b bit set: a prefix
+// per 256 bits plus popcounts of the bits before the node.  In other levels it
+// is its position in the ascending frontier, which k_sage_places notes at the
+// node's N_b row.
 #include <hip/hip_fp16.h>
 
 #include "gg_host.hpp"
@@ -24,376 +30,882 @@ namespace gg {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kSageBlock = 256;          // 4 waves
 constexpr int kTileRows = 64;            // 16 rows per wave
-constexpr int kWLdsFloats = 16384;       // 64 KB of weights in LDS at most
-constexpr int kRankChunk = 2048;         // bit-set words per rank chunk (divides gg_bits_words)
+constexpr int kGroup = 16;               // columns of the left operand per MFMA group
+constexpr int kWLdsBytes = 65536;        // weights in LDS at most (two blocks per CU)
+constexpr int kRankWords = 4;            // bit-set words per rank prefix
+constexpr int kRankChunk = kSageBlock * 2 * kRankWords;   // words per rank chunk
+constexpr int kMaxPitch = GG_MAX_FANOUT + 1;
+static_assert(kRankChunk == kChunkWords, "rank chunks divide gg_bits_words");
 
-// ---------------------------------------------------------------------------
-// Rank of a node in its batch's N_b bit set.
-// ---------------------------------------------------------------------------
+// Packed weights of one layer: for MFMA group q, then W_self and W_neigh, then
+// column tile t, lane l's four values W[k0 + e][16 t + l % 16], e = 0..3 (zero
+// past the layer's sizes; k0 = 16 q + 4 (l / 16)): one 16-byte read feeds
+// four MFMA steps.
+struct PackArgs {
+  const float* w[GG_MAX_LAYERS][2];
+  int32_t d_in[GG_MAX_LAYERS], d_out[GG_MAX_LAYERS], nt[GG_MAX_LAYERS];
+  int64_t first[GG_MAX_LAYERS + 1];   // first packed f32x4 of each layer
+  int32_t L;
+};
 
-// rank[w] = {set bits of the words before w inside w's chunk, word w}: the
-// word travels with its prefix so that a rank lookup is one 8-byte load;
-// csum[b][c] = bits of chunk c of batch b.
-__global__ void __launch_bounds__(kSageBlock) k_rank_local(const uint32_t* bits, int64_t wpb,
-                                                           int64_t nch, int2* rank,
-                                                           int32_t* csum) {
+// Blocks below nch * W: the rank prefixes of chunk c of batch b (rank[w / 4] =
+// set bits of the batch's set before word w).  The bits before the chunk are
+// the entries of the batch's ascending list N_b below the chunk's first id,
+// which the first wave finds in three or four rounds of 64 probes; summing the
+// chunks' bits would take a launch of its own and a second lookup per rank.
+// The other blocks pack the weights.
+__global__ void __launch_bounds__(kSageBlock) k_sage_prepare(const uint32_t* bits, int32_t nch,
+                                                             const int32_t* fids,
+                                                             const int64_t* nb_off, int32_t W,
+                                                             int2* rank, PackArgs pk,
+                                                             f32x4* packed) {
   __shared__ int32_t lds[kSageBlock / kWave];
-  const int b = blockIdx.y;
-  const int64_t c = blockIdx.x;
-  const int64_t w0 = (int64_t)b * wpb + c * kRankChunk + (int64_t)threadIdx.x * 8;
-  uint32_t wd[8];
-  int32_t s = 0;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    wd[j] = bits[w0 + j];
-    s += __popc(wd[j]);
-  }
-  int32_t tot;
-  int32_t run = block_excl_scan<kSageBlock>(s, lds, &tot);
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    rank[w0 + j] = make_int2(run, (int32_t)wd[j]);
-    run += __popc(wd[j]);
-  }
-  if (threadIdx.x == 0) csum[(int64_t)b * nch + c] = tot;
-}
-
-// Exclusive scan of each batch's chunk counts, in place.
-__global__ void __launch_bounds__(kSageBlock) k_rank_chunks(int32_t* csum, int64_t nch) {
-  __shared__ int32_t lds[kSageBlock / kWave];
-  int32_t* cs = csum + (int64_t)blockIdx.x * nch;
-  int32_t carry = 0;
-  for (int64_t i0 = 0; i0 < nch; i0 += kSageBlock) {
-    const int64_t i = i0 + threadIdx.x;
-    const int32_t v = i < nch ? cs[i] : 0;
+  __shared__ int64_t s_first;
+  const int64_t nrank = (int64_t)nch * W;
+  if ((int64_t)blockIdx.x < nrank) {
+    const int64_t bc = blockIdx.x;   // b * nch + c: the chunks of all sets back to back
+    const u32x4* p = (const u32x4*)(bits + bc * kRankChunk) + threadIdx.x * 2;
+    const u32x4 x = p[0], y = p[1];
+    if (threadIdx.x < kWave) {
+      const int b = (int)(bc / nch);
+      const int32_t key = (int32_t)(bc - (int64_t)b * nch) * (kRankChunk * 32);
+      const int32_t* list = fids + nb_off[b];
+      int64_t lo = 0, hi = nb_off[b + 1] - nb_off[b];
+      while (lo < hi) {
+        const int64_t step = (hi - lo + kWave - 1) / kWave;
+        const int64_t at = lo + step * threadIdx.x;
+        const int below = (int)__popcll(__ballot(at < hi && list[at < hi ? at : lo] < key));
+        if (below == 0) break;
+        const int64_t first = lo + (int64_t)(below - 1) * step + 1;
+        hi = lo + (int64_t)below * step < hi ? lo + (int64_t)below * step : hi;
+        lo = first;
+      }
+      if (threadIdx.x == 0) s_first = lo;
+    }
+    const int32_t sx = __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
+    const int32_t sy = __popc(y.x) + __popc(y.y) + __popc(y.z) + __popc(y.w);
     int32_t tot;
-    const int32_t ex = block_excl_scan<kSageBlock>(v, lds, &tot);
-    if (i < nch) cs[i] = carry + ex;
-    carry += tot;
-    __syncthreads();
+    const int32_t before = block_excl_scan<kSageBlock>(sx + sy, lds, &tot) + (int32_t)s_first;
+    rank[bc * kSageBlock + threadIdx.x] = make_int2(before, before + sx);
+    return;
+  }
+  const int64_t total = pk.first[pk.L];
+  for (int64_t i = (blockIdx.x - nrank) * kSageBlock + threadIdx.x; i < total;
+       i += (gridDim.x - nrank) * kSageBlock) {
+    int j = 0;
+    while (j + 1 < pk.L && i >= pk.first[j + 1]) ++j;
+    const int32_t e = (int32_t)(i - pk.first[j]);
+    const int nt = pk.nt[j], lane = e % kWave, r = e / kWave;
+    const int t = r % nt, sn = r / nt % 2, q = r / nt / 2;
+    const int col = t * 16 + (lane & 15), k0 = q * kGroup + 4 * (lane >> 4);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (col < pk.d_out[j])
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+        if (k0 + a < pk.d_in[j]) v[a] = pk.w[j][sn][(int64_t)(k0 + a) * pk.d_out[j] + col];
+    packed[i] = v;
   }
 }
 
 // ---------------------------------------------------------------------------
-// Projection Z = H [W_self | W_neigh] on MFMA.
+// Input rows of every output node.
 // ---------------------------------------------------------------------------
-struct ProjArgs {
-  const char* h;        // input rows of the level, back to back
-  int64_t h_stride;     // bytes
-  int32_t K;            // d_in
-  int32_t K16;          // K rounded up to 16
-  int32_t kc;           // weight rows per LDS chunk (multiple of 16)
-  int32_t d_out;
-  int32_t ldz;          // floats per Z row (NT * 16)
-  const float* w_self;  // [K][d_out]
-  const float* w_neigh;
-  float* z;
-  const int64_t* off;   // frontier_off
-  int64_t seg0;         // first segment of the input level
-  int32_t W;
+struct RowsArgs {
+  int32_t W, L;
+  int32_t k[GG_MAX_LAYERS];            // by level
+  uint32_t kmagic[GG_MAX_LAYERS];      // div_magic(k + 1)
+  int32_t* table[GG_MAX_LAYERS];       // [rows of level l][k + 1]: self, then the slots
+  int32_t* place[GG_MAX_LAYERS];       // level l >= 1: N_b row -> position in the batch's F_l
+  const int32_t* fids;
+  const int64_t* off;                  // frontier_off
+  const int32_t* nbr;
+  const int64_t* noff;
+  const uint32_t* bits;
+  const int32_t* rank;
+  int64_t wpb;
   int64_t rows_cap;
 };
 
-// Four consecutive elements of a row starting at column c (zero past K).
-template <int XT, bool VEC>
-__device__ __forceinline__ f32x4 load4(const char* row, int c, int K) {
-  f32x4 v = {0.f, 0.f, 0.f, 0.f};
-  if (VEC && c + 3 < K) {
-    if (XT == GG_F32) {
-      v = *(const f32x4*)(row + (int64_t)c * 4);
-    } else {
-      const __half2* p = (const __half2*)(row + (int64_t)c * 2);
-      const float2 lo = __half22float2(p[0]), hi = __half22float2(p[1]);
-      v = f32x4{lo.x, lo.y, hi.x, hi.y};
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (c + e < K)
-        v[e] = XT == GG_F32 ? ((const float*)row)[c + e]
-                            : __half2float(((const __half*)row)[c + e]);
-  }
-  return v;
-}
-
-// The contraction over K is evaluated in a permuted order: in the 16-column
-// group q, lane group g = lane / 16 holds columns q + 4g .. q + 4g + 3 of its
-// row (one 16-byte load) and feeds them to four MFMA steps, while the B
-// operand of lane 16g + j is the weight row with the same column index.
-// Every product A[i][k] B[k][j] is taken exactly once.
-template <int NT, int XT, bool VEC>
-__global__ void __launch_bounds__(kSageBlock) k_sage_project(ProjArgs a, int32_t* status) {
-  extern __shared__ float Ws[];   // a.kc rows of NT * 16 weights
-  constexpr int ncol = NT * 16;
-  int64_t n = a.off[a.seg0 + a.W] - a.off[a.seg0];
-  if (n > a.rows_cap) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) set_status(status, GG_DEV_CAPACITY);
-    n = a.rows_cap;
-  }
-  const int lane = lane_id();
-  const int wv = (int)threadIdx.x / kWave;
-  const int g = lane >> 4, il = lane & 15;
-  const int n2 = 2 * a.d_out;
-  const bool whole = a.kc >= a.K16;
-  auto load_w = [&](int k0) {
-    for (int e = threadIdx.x; e < a.kc * ncol; e += kSageBlock) {
-      const int kk = e / ncol, c = e - kk * ncol;
-      const int k = k0 + kk;
-      float v = 0.f;
-      if (k < a.K) {
-        if (c < a.d_out)
-          v = a.w_self[(int64_t)k * a.d_out + c];
-        else if (c < n2)
-          v = a.w_neigh[(int64_t)k * a.d_out + (c - a.d_out)];
-      }
-      Ws[e] = v;
-    }
-  };
-  if (whole) {
-    load_w(0);
-    __syncthreads();
-  }
-  for (int64_t row0 = (int64_t)blockIdx.x * kTileRows; row0 < n;
-       row0 += (int64_t)gridDim.x * kTileRows) {
-    const int64_t r = row0 + wv * 16 + il;
-    const bool rok = r < n;
-    const char* rp = a.h + (rok ? r : 0) * a.h_stride;
-    f32x4 acc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < a.K16; k0 += a.kc) {
-      if (!whole) {
-        __syncthreads();
-        load_w(k0);
-        __syncthreads();
-      }
-      const int kend = a.K16 - k0 < a.kc ? a.K16 - k0 : a.kc;
-      constexpr int U = 4;   // 16-column groups whose loads are issued together
-      for (int q = 0; q < kend; q += 16 * U) {
-        f32x4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int qq = q + 16 * u;
-          v[u] = (rok && qq < kend) ? load4<XT, VEC>(rp, k0 + qq + 4 * g, a.K)
-                                    : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int qq = q + 16 * u;
-          if (qq >= kend) break;
-          const float* wrow = Ws + (int64_t)(qq + 4 * g) * ncol + il;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-              acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[u][e], wrow[e * ncol + t * 16],
-                                                            acc[t], 0, 0, 0);
-          }
-        }
-      }
-    }
-    // D[i][j] of tile t sits in lane 16 * (i / 4) + j, element i % 4.
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int col = t * 16 + il;
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const int64_t row = row0 + wv * 16 + 4 * g + rr;
-        if (row < n && col < n2) a.z[row * a.ldz + col] = acc[t][rr];
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Mean aggregation of the projected rows.
-// ---------------------------------------------------------------------------
-struct AggArgs {
-  const int32_t* fids;
-  const int64_t* off;
-  const int32_t* nbr;
-  const int64_t* noff;
-  int32_t W;
-  int32_t lvl;          // output level; the input level is lvl + 1
-  int32_t k;            // fanout of hop lvl
-  const float* z;
-  int32_t ldz;
-  int32_t d_out;
-  const float* bias;
-  int32_t relu;
-  float* out;           // output rows of level lvl, back to back, d_out floats each
-  int64_t z_cap;        // rows of z that were computed
-  int64_t out_cap;
-  // rank lookup in the N_b bit sets (input level = N_b), else binary search
-  int32_t use_rank;
-  const int2* rank;     // {prefix in chunk, word} per bit-set word
-  const int32_t* cpre;
-  int64_t wpb;
-  int64_t nch;
+// One batch's part of a level: where its entries, its slots, its N_b and its
+// ranks lie.
+struct Batch {
+  int64_t out0, out1;      // entries of the output level, relative to the level's first
+  int64_t in0, nin;        // entries of the input level: first (absolute), count
+  int64_t nb0, nnb;        // N_b: first row, count
+  int64_t slot0, nslot;    // the hop's neighbour slots: first (absolute), count
+  const u32x4* bits;       // 128-bit groups of the batch's set
+  const int32_t* rank;     // set bits before each group
 };
 
-__device__ __forceinline__ int64_t find_sorted(const int32_t* a, int64_t n, int32_t v) {
-  int64_t lo = 0, hi = n;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (a[mid] < v)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  return (lo < n && a[lo] == v) ? lo : -1;
+__device__ __forceinline__ Batch batch_at(const RowsArgs& a, int lvl, int b) {
+  const int64_t s = (int64_t)lvl * a.W + b, sn = (int64_t)a.L * a.W;
+  Batch t;
+  const int64_t o0 = a.off[(int64_t)lvl * a.W];
+  t.out0 = a.off[s] - o0;
+  t.out1 = a.off[s + 1] - o0;
+  t.in0 = a.off[s + a.W];
+  t.nin = a.off[s + a.W + 1] - t.in0;
+  t.nb0 = a.off[sn + b] - a.off[sn];
+  t.nnb = a.off[sn + b + 1] - a.off[sn + b];
+  t.slot0 = a.noff[s];
+  t.nslot = a.noff[s + 1] - t.slot0;
+  t.bits = (const u32x4*)(a.bits + (int64_t)b * a.wpb);
+  t.rank = a.rank + (int64_t)b * (a.wpb / kRankWords);
+  return t;
 }
 
-__device__ __forceinline__ int32_t row_in_level(const AggArgs& a, int b, const int32_t* Fin,
-                                                int64_t nin, int32_t u) {
-  int64_t p;
-  if (a.use_rank) {
-    const int64_t wi = (int64_t)(uint32_t)u >> 5;
-    if (u < 0 || wi >= a.wpb) return -1;
-    const int64_t w = (int64_t)b * a.wpb + wi;
-    const int2 rw = a.rank[w];
-    const int32_t cpre = a.cpre[(int64_t)b * a.nch + wi / kRankChunk];
-    const uint32_t word = (uint32_t)rw.y, bit = 1u << (u & 31);
-    if (!(word & bit)) return -1;
-    p = (int64_t)rw.x + cpre + __popc(word & (bit - 1u));
-    if (p >= nin) return -1;
-  } else {
-    p = find_sorted(Fin, nin, u);
-  }
-  return (int32_t)p;
+// Batch of entry r of the level (off: the level's W + 1 offsets in LDS,
+// relative, padded with INT64_MAX).
+__device__ __forceinline__ int batch_of(const int64_t* off, int64_t r) {
+  int b = 0;
+#pragma unroll
+  for (int step = 32; step >= 1; step >>= 1)
+    if (off[b + step] <= r) b += step;
+  return b;
 }
 
-// Grid (blocks, W): block column b serves batch b.  Sixteen lanes per output
-// node: lane j of the group resolves neighbour slots j and j + 16, then the
-// group sums the projected neighbour rows, 16 columns at a time.  The
-// neighbour loop is unrolled to KMAX >= k so that all of a column's row
-// loads are in flight together; the sum still runs in slot order.
-template <int KMAX>
-__global__ void __launch_bounds__(kSageBlock) k_sage_aggregate(AggArgs a, int32_t* status) {
-  const int b = blockIdx.y;
-  const int64_t sout = (int64_t)a.lvl * a.W + b, sin = sout + a.W;
-  const int64_t o0 = a.off[sout], nout = a.off[sout + 1] - o0;
-  const int64_t i0 = a.off[sin], nin = a.off[sin + 1] - i0;
-  const int64_t orow0 = o0 - a.off[(int64_t)a.lvl * a.W];
-  const int64_t zrow0 = i0 - a.off[(int64_t)(a.lvl + 1) * a.W];
-  const int32_t* Fin = a.fids + i0;
-  const int32_t* Fout = a.fids + o0;
-  const int32_t* S = a.nbr + a.noff[sout];
-  const int64_t nslots = a.noff[sout + 1] - a.noff[sout];   // nout * k unless clamped
-  const int lane = lane_id();
-  const int sub = (int)threadIdx.x >> 4, sl = (int)threadIdx.x & 15;
-  const int gbase = lane & 48;   // first lane of this group within the wave
+// Rank of u among the set's n bits, from its 128-bit group and the bits before
+// that group; -1 when its bit is clear.
+__device__ __forceinline__ int64_t rank_in(u32x4 x, int32_t pre, int32_t u, int64_t n) {
+  const uint32_t w[kRankWords] = {x.x, x.y, x.z, x.w};
+  const uint32_t in = ((uint32_t)u >> 5) % kRankWords, bit = 1u << (u & 31);
+  uint32_t mine = 0;
+  int32_t before = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < kRankWords; ++j) {
+    before += j < in ? __popc(w[j]) : 0;
+    mine = j == in ? w[j] : mine;
+  }
+  const int64_t r = (int64_t)pre + before + __popc(mine & (bit - 1u));
+  return (mine & bit) && r < n ? r : -1;
+}
+
+// Position of u in the batch's N_b, or -1.
+__device__ __forceinline__ int64_t rank_of(const Batch& t, int64_t wpb, int32_t u) {
+  const uint32_t wi = (uint32_t)u >> 5;
+  if (u < 0 || wi >= (uint64_t)wpb) return -1;
+  return rank_in(t.bits[wi / kRankWords], t.rank[wi / kRankWords], u, t.nnb);
+}
+
+__device__ __forceinline__ void level_offsets(const RowsArgs& a, int lvl, int64_t* off) {
+  for (int t = threadIdx.x; t <= GG_MAX_W; t += kSageBlock)
+    off[t] = t <= a.W ? a.off[(int64_t)lvl * a.W + t] - a.off[(int64_t)lvl * a.W] : INT64_MAX;
+  __syncthreads();
+}
+
+// Level blockIdx.y + 1 (1..L-1): each node's position, noted at its N_b row.
+__global__ void __launch_bounds__(kSageBlock) k_sage_places(RowsArgs a) {
+  __shared__ int64_t off[GG_MAX_W + 1];
+  const int lvl = blockIdx.y + 1;
+  level_offsets(a, lvl, off);
+  const int64_t n = off[a.W], f0 = a.off[(int64_t)lvl * a.W];
+  for (int64_t r = (int64_t)blockIdx.x * kSageBlock + threadIdx.x; r < n;
+       r += (int64_t)gridDim.x * kSageBlock) {
+    const Batch t = batch_at(a, lvl, batch_of(off, r));
+    const int64_t p = rank_of(t, a.wpb, a.fids[f0 + r]);
+    if (p >= 0 && t.nb0 + p < a.rows_cap) a.place[lvl][t.nb0 + p] = (int32_t)(r - t.out0);
+  }
+}
+
+// J entries of a tile at a time, each stage's loads issued together: node ids,
+// then set words and prefixes, then (below the top level) places, then the
+// frontier entries that confirm them.
+constexpr int kRowTile = 64;            // rows of a table tile
+constexpr int kRowJ = 3;                 // entries in flight per lane
+
+__device__ __forceinline__ void find_rows(const RowsArgs& a, int lvl, int64_t f0, int64_t f0in,
+                                          const Batch* bt, const int64_t (&r)[kRowJ],
+                                          const int (&t)[kRowJ], const bool (&in)[kRowJ],
+                                          int32_t (&row)[kRowJ], int32_t& st) {
+  int32_t u[kRowJ], pre[kRowJ];
+  u32x4 x[kRowJ];
+  bool ask[kRowJ];
+#pragma unroll
+  for (int j = 0; j < kRowJ; ++j) {
+    u[j] = -1;
+    if (in[j]) {
+      const int64_t q = (r[j] - bt->out0) * a.k[lvl] + (t[j] - 1);   // slot of the batch's list
+      if (t[j] == 0)
+        u[j] = a.fids[f0 + r[j]];
+      else if (q < bt->nslot)
+        u[j] = a.nbr[bt->slot0 + q];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kRowJ; ++j) {
+    const uint32_t wi = (uint32_t)u[j] >> 5;
+    ask[j] = u[j] >= 0 && wi < (uint64_t)a.wpb;
+    pre[j] = 0;
+    x[j] = u32x4{0u, 0u, 0u, 0u};
+    if (ask[j]) {
+      x[j] = bt->bits[wi / kRankWords];
+      pre[j] = bt->rank[wi / kRankWords];
+    }
+  }
+  int64_t at[kRowJ];
+  bool found[kRowJ];
+#pragma unroll
+  for (int j = 0; j < kRowJ; ++j) {
+    const int64_t p = ask[j] ? rank_in(x[j], pre[j], u[j], bt->nnb) : -1;
+    found[j] = p >= 0;
+    at[j] = bt->nb0 + p;
+  }
+  if (lvl + 1 < a.L) {
+    // a place is trusted only if the frontier entry it names is the node
+    int64_t pl[kRowJ];
+#pragma unroll
+    for (int j = 0; j < kRowJ; ++j)
+      pl[j] = found[j] && at[j] < a.rows_cap ? a.place[lvl + 1][at[j]] : -1;
+#pragma unroll
+    for (int j = 0; j < kRowJ; ++j)
+      if (found[j] && at[j] < a.rows_cap) {
+        found[j] = pl[j] >= 0 && pl[j] < bt->nin && a.fids[bt->in0 + pl[j]] == u[j];
+        at[j] = bt->in0 - f0in + pl[j];
+      }
+  }
+#pragma unroll
+  for (int j = 0; j < kRowJ; ++j) {
+    row[j] = found[j] && at[j] < a.rows_cap ? (int32_t)at[j] : -1;
+    if (in[j] && !found[j] && (u[j] >= 0 || t[j] == 0)) st |= GG_DEV_BAD_ID;
+  }
+}
+
+// Level blockIdx.y (0..L-1): the row, in the level above, of entry t of each
+// node (t = 0: itself, t = 1..k: its neighbour slots), or -1.  Bound by the
+// latency of its dependent random reads.  Nearly all tiles lie in one batch,
+// whose addresses are then the same for every lane.
+__global__ void __launch_bounds__(kSageBlock) k_sage_rows(RowsArgs a, int32_t* status) {
+  __shared__ int64_t off[GG_MAX_W + 1];
+  const int lvl = a.L - 1 - (int)blockIdx.y;   // the largest level first
+  level_offsets(a, lvl, off);
+  const int64_t n = off[a.W] < a.rows_cap ? off[a.W] : a.rows_cap;
+  const int64_t f0 = a.off[(int64_t)lvl * a.W], f0in = a.off[(int64_t)(lvl + 1) * a.W];
+  const int k = a.k[lvl];
   int32_t st = 0;
-  for (int64_t i = (int64_t)blockIdx.x * (kSageBlock / 16) + sub; i < nout;
-       i += (int64_t)gridDim.x * (kSageBlock / 16)) {
-    int32_t pv = row_in_level(a, b, Fin, nin, Fout[i]);
-    int32_t p0 = -1, p1 = -1;
-    if (sl < a.k && i * a.k + sl < nslots) {
-      const int32_t u = S[i * a.k + sl];
-      if (u >= 0) {
-        p0 = row_in_level(a, b, Fin, nin, u);
-        if (p0 < 0) st |= GG_DEV_BAD_ID;
-      }
-    }
-    if (sl + 16 < a.k && i * a.k + sl + 16 < nslots) {
-      const int32_t u = S[i * a.k + sl + 16];
-      if (u >= 0) {
-        p1 = row_in_level(a, b, Fin, nin, u);
-        if (p1 < 0) st |= GG_DEV_BAD_ID;
-      }
-    }
-    if (pv < 0) st |= GG_DEV_BAD_ID;
-    if (zrow0 + pv >= a.z_cap) pv = -1;
-    if (p0 >= 0 && zrow0 + p0 >= a.z_cap) p0 = -1;
-    if (p1 >= 0 && zrow0 + p1 >= a.z_cap) p1 = -1;
-    int32_t pt[KMAX];
-    int cnt = 0;
+  for (int64_t row0 = (int64_t)blockIdx.x * kRowTile; row0 < n;
+       row0 += (int64_t)gridDim.x * kRowTile) {
+    const int b = __builtin_amdgcn_readfirstlane(batch_of(off, row0));
+    const Batch bt = batch_at(a, lvl, b);
+    const int rows = (int)(n - row0 < kRowTile ? n - row0 : kRowTile);
+    const int total = rows * (k + 1);
+    int32_t* out = a.table[lvl] + row0 * (k + 1);
+    const bool one = row0 + rows <= bt.out1;
+    for (int e0 = threadIdx.x; e0 < total; e0 += kSageBlock * kRowJ) {
+      int64_t r[kRowJ];
+      int t[kRowJ];
+      bool in[kRowJ];
+      int32_t row[kRowJ];
 #pragma unroll
-    for (int t = 0; t < KMAX; ++t) {
-      pt[t] = __shfl(t < 16 ? p0 : p1, gbase + (t & 15), kWave);
-      if (t >= a.k) pt[t] = -1;
-      cnt += pt[t] >= 0;
-    }
-    const float inv = cnt ? 1.0f / (float)cnt : 0.f;
-    const int64_t orow = orow0 + i;
-    for (int c0 = 0; c0 < a.d_out; c0 += 16) {
-      const int c = c0 + sl;
-      const bool cok = c < a.d_out;
-      const float self = (cok && pv >= 0) ? a.z[(zrow0 + pv) * a.ldz + c] : 0.f;
-      float v[KMAX];
-#pragma unroll
-      for (int t = 0; t < KMAX; ++t)
-        v[t] = (cok && pt[t] >= 0) ? a.z[(zrow0 + pt[t]) * a.ldz + a.d_out + c] : 0.f;
-      float sum = 0.f;
-#pragma unroll
-      for (int t = 0; t < KMAX; ++t)
-        if (pt[t] >= 0) sum += v[t];
-      if (cok && pv >= 0) {
-        float y = self + sum * inv + (a.bias ? a.bias[c] : 0.f);
-        if (a.relu && y < 0.f) y = 0.f;
-        if (orow < a.out_cap) a.out[orow * a.d_out + c] = y;
+      for (int j = 0; j < kRowJ; ++j) {
+        const int e = e0 + j * kSageBlock;
+        const int rr = (int)chunk_row((uint32_t)e, a.kmagic[lvl]);
+        in[j] = e < total;
+        r[j] = row0 + rr;
+        t[j] = e - rr * (k + 1);
       }
+      if (one) {
+        find_rows(a, lvl, f0, f0in, &bt, r, t, in, row, st);
+      } else {
+        // every lane goes through the batches its tile touches
+        for (int bb = b; bb < a.W && off[bb] < row0 + rows; ++bb) {
+          const Batch ob = batch_at(a, lvl, bb);
+          bool mine[kRowJ];
+          int32_t got[kRowJ];
+#pragma unroll
+          for (int j = 0; j < kRowJ; ++j)
+            mine[j] = in[j] && r[j] >= ob.out0 && r[j] < ob.out1;
+          find_rows(a, lvl, f0, f0in, &ob, r, t, mine, got, st);
+#pragma unroll
+          for (int j = 0; j < kRowJ; ++j) row[j] = mine[j] ? got[j] : row[j];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < kRowJ; ++j)
+        if (in[j]) out[e0 + j * kSageBlock] = row[j];
     }
-    if (orow >= a.out_cap) st |= GG_DEV_CAPACITY;
   }
   if (st) set_status(status, st);
 }
 
-int ldz_tiles(int32_t d_out) {
-  const int need = (2 * d_out + 15) / 16;
-  int nt = 1;
-  while (nt < need) nt <<= 1;
-  return nt;
+// What one lane loads of a row: 16 bytes, VE = 4 (fp32) or 8 (fp16) consecutive
+// columns, kept as loaded while in flight.
+template <int XT>
+struct Cols {
+  static constexpr int VE = XT == GG_F32 ? 4 : 8;
+  float v[VE];
+};
+
+__device__ __forceinline__ u32x4 load16(const char* p) {
+  typedef u32x4 __attribute__((aligned(2))) any;
+  return *(const GG_GLOBAL any*)p;
+}
+
+// The same for a row of fewer than VE elements: zeros past its last word or
+// half word.
+template <int XT>
+__device__ __forceinline__ u32x4 load_narrow(const char* row, int c, int K) {
+  constexpr int VE = Cols<XT>::VE;
+  u32x4 r = {0u, 0u, 0u, 0u};
+  if (c > 0) return r;
+#pragma unroll
+  for (int e = 0; e < VE; ++e)
+    if (e < K) {
+      if constexpr (XT == GG_F32)
+        r[e] = ((const GG_GLOBAL uint32_t*)row)[e];
+      else
+        r[e / 2] |= (uint32_t)((const GG_GLOBAL uint16_t*)row)[e] << (16 * (e & 1));
+    }
+  return r;
+}
+
+template <int XT>
+__device__ __forceinline__ float element(u32x4 r, int e) {
+  if constexpr (XT == GG_F32) {
+    return __builtin_bit_cast(f32x4, r)[e];
+  } else {
+    return (float)__builtin_bit_cast(f16x8, r)[e];
+  }
+}
+
+// r holds the VE elements that end at the row's last one, s > 0 past the
+// wanted first: shifts them into place, zeros behind.
+template <int XT>
+__device__ __forceinline__ void shift_cols(Cols<XT>& r, int s) {
+  constexpr int VE = Cols<XT>::VE;
+  if (s <= 0) return;
+#pragma unroll
+  for (int step = 1; step < VE; step <<= 1)
+#pragma unroll
+    for (int e = 0; e < VE; ++e) {
+      const float up = e + step < VE ? r.v[e + step] : 0.f;
+      r.v[e] = (s & step) ? up : r.v[e];
+    }
+  if (s >= VE)
+#pragma unroll
+    for (int e = 0; e < VE; ++e) r.v[e] = 0.f;
+}
+
+// ---------------------------------------------------------------------------
+// One layer: gather, mean and product.
+// ---------------------------------------------------------------------------
+struct LayerArgs {
+  const char* h;        // input rows of the level, back to back
+  int64_t h_stride;     // bytes
+  int32_t K;            // columns to load per row
+  int32_t G;            // MFMA groups (packed)
+  const f32x4* w;       // packed weights, 2 * NT * 64 per group
+  int32_t k;            // fanout of the hop
+  const int32_t* table; // [rows][k + 1]
+  const int64_t* off;   // frontier_off at the output level
+  int32_t W;
+  const float* bias;
+  int32_t d_out, relu;
+  int32_t ncols;        // columns stored per row (d_out, or padded with zeros)
+  float* out;           // output rows of the level, back to back, ncols floats each
+  int64_t rows_cap, out_cap;
+};
+
+// Sets GG_DEV_CAPACITY when the input or the output level does not fit.
+__device__ __forceinline__ int64_t level_rows(const int64_t* off, int W, int64_t rows_cap,
+                                              int64_t out_cap, int32_t* status) {
+  const int64_t n = off[W] - off[0], nin = off[2 * W] - off[W];
+  if (blockIdx.x == 0 && threadIdx.x == 0 && (nin > rows_cap || n > out_cap))
+    set_status(status, GG_DEV_CAPACITY);
+  const int64_t cap = out_cap < rows_cap ? out_cap : rows_cap;
+  return n < cap ? n : cap;
+}
+
+// How a block's four waves share the tile's product: R output rows, split RW
+// ways by rows and CW by columns, RT x CT MFMA tiles each.
+template <int NT>
+struct Split {
+  static constexpr int R = NT <= 3 ? 64 : 32;
+  static constexpr int CW = NT <= 3 ? 1 : (NT == 6 ? 2 : 4);
+  static constexpr int RW = 4 / CW;
+  static constexpr int CT = NT / CW;
+  static constexpr int RT = R / 16 / RW;
+};
+
+// A block takes tiles of R output rows, S = LR * VE columns at a time: it
+// gathers the columns of [h_v | mean h_u] into LDS, LR lanes per source row,
+// so that a load covers runs of 16 * LR bytes (a row in shorter runs fetches
+// the lines at their ends again, once the caches have dropped them), then
+// multiplies them by the packed weights, which every block finds in L2.  Two
+// or three blocks per CU gather and multiply in turn.  The row tables come to
+// LDS one tile ahead.  Products are summed four groups at a time and then
+// added to the running sums, which keeps the rounding error below one long
+// sum's.
+//
+// Wide rows are bound by the random row reads (262K x 602 fp32 -> 128, ten
+// neighbours, 77K outputs: 549 us for 2.1 GB of row reads, where projecting
+// every row by [W_self | W_neigh], whose 85 GFLOP the fp32 matrix cores need
+// 550 us for at best, took 2,447 + 119), narrow ones by matrix work (1.4M x
+// 128 fp16 -> 128, five neighbours: 234 us, 117 of them matrix cores at full
+// rate; projected 1,676 + 232).  Also measured on the first: the lookups of
+// k_sage_rows inside the tile loop and 64-byte runs 655; half the waves
+// gathering and half multiplying 858; 1 KB runs in two blocks per CU 594;
+// eight neighbour rows in flight instead of five, in two blocks per CU, 565.
+// Blocks of three column tiles or fewer keep to two per CU: their registers
+// do not fit three without spills.
+template <int NT, int XT, int LR, bool NARROW>
+__global__ void __launch_bounds__(kSageBlock, NT <= 3 ? 2 : 3) k_sage_layer(LayerArgs a, int32_t* status) {
+  typedef Split<NT> Sp;
+  constexpr int VE = Cols<XT>::VE, ES = 16 / VE;
+  constexpr int S = LR * VE;                 // columns per pass
+  constexpr int LD = S + 4;                  // padded against bank conflicts
+  constexpr int RG = kWave / LR;             // rows per load
+  constexpr int RPW = Sp::R / 4;             // rows a wave gathers
+  constexpr int NRG = (RPW + RG - 1) / RG;
+  constexpr int RB = NRG >= 2 ? 2 : 1;       // row groups in flight
+  constexpr int TU = 5;                      // ... with so many neighbour rows each
+  constexpr int kTab = (Sp::R * kMaxPitch + kSageBlock - 1) / kSageBlock;
+  extern __shared__ float sm[];
+  float* A = sm;                             // [2][R][LD]: self, mean
+  int32_t* s_pos = (int32_t*)(sm + 2 * Sp::R * LD);   // [2][R * pitch]
+  const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+  const int64_t n = level_rows(a.off, a.W, a.rows_cap, a.out_cap, status);
+  const int pitch = a.k + 1;
+  const bool any = a.off[2 * a.W] - a.off[a.W] > 0 && a.rows_cap > 0;   // input rows
+  if (!any) return;
+  const int npass = (a.K + S - 1) / S;
+  const int64_t step = (int64_t)gridDim.x * Sp::R;
+  int64_t row0 = (int64_t)blockIdx.x * Sp::R;
+  const int tabn = Sp::R * pitch;
+
+  int32_t tab[kTab];
+  auto fetch_table = [&](int64_t r0) {
+    const int64_t left = (n - r0) * pitch;
+#pragma unroll
+    for (int j = 0; j < kTab; ++j) {
+      const int e = j * kSageBlock + tid;
+      if (j * kSageBlock < tabn) tab[j] = (e < tabn && e < left) ? a.table[r0 * pitch + e] : -1;
+    }
+  };
+  auto store_table = [&](int par) {
+#pragma unroll
+    for (int j = 0; j < kTab; ++j) {
+      const int e = j * kSageBlock + tid;
+      if (e < tabn) s_pos[par * tabn + e] = tab[j];
+    }
+  };
+  fetch_table(row0);
+  store_table(0);
+  __syncthreads();
+
+  const int lr = lane / LR, lc = lane % LR, c = lc * VE;
+  const int g = lane >> 4, il = lane & 15;
+  const int rt0 = wv / Sp::CW * Sp::RT, ct0 = wv % Sp::CW * Sp::CT;
+  int par = 0;
+  for (; row0 < n; row0 += step, par ^= 1) {
+    const int32_t* pos = s_pos + par * tabn;
+    f32x4 tot[Sp::RT][Sp::CT];
+#pragma unroll
+    for (int r = 0; r < Sp::RT; ++r)
+#pragma unroll
+      for (int t = 0; t < Sp::CT; ++t) tot[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int ps = 0; ps < npass; ++ps) {
+      // ---- gather ----
+      const int col = ps * S + c;
+      const int off = (col < a.K - VE ? col : a.K - VE) * ES;
+      const int past = col + VE - a.K;       // > 0: the row ends before the lane's columns do
+      auto load = [&](int32_t p) {
+        const char* rp = a.h + (int64_t)(p > 0 ? p : 0) * a.h_stride;
+        return NARROW ? load_narrow<XT>(rp, c, a.K) : load16(rp + off);
+      };
+#pragma unroll 1
+      for (int q = 0; q < NRG; q += RB) {
+        const int32_t* rp[RB];
+        int m = 0;
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+          const int r = (q + i) * RG + lr;
+          rp[i] = pos + (wv * RPW + (r < RPW ? r : RPW - 1)) * pitch;
+          for (int t = lc; t < a.k; t += LR)
+            if (rp[i][1 + t] >= 0) m = max(m, t + 1);
+        }
+#pragma unroll
+        for (int o = kWave / 2; o >= 1; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
+        const int tmax = __builtin_amdgcn_readfirstlane(m);
+        u32x4 own[RB], v[RB * TU];
+        Cols<XT> sum[RB];
+        int cnt[RB];
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+          own[i] = load(rp[i][0]);
+          cnt[i] = 0;
+#pragma unroll
+          for (int e = 0; e < VE; ++e) sum[i].v[e] = 0.f;
+        }
+        for (int t0 = 0; t0 < tmax; t0 += TU) {
+#pragma unroll
+          for (int j = 0; j < TU; ++j)
+            if (t0 + j < tmax)
+#pragma unroll
+              for (int i = 0; i < RB; ++i) v[i * TU + j] = load(rp[i][1 + t0 + j]);
+#pragma unroll
+          for (int j = 0; j < TU; ++j)
+            if (t0 + j < tmax)
+#pragma unroll
+              for (int i = 0; i < RB; ++i) {
+                const bool ok = rp[i][1 + t0 + j] >= 0;
+                cnt[i] += ok;
+#pragma unroll
+                for (int e = 0; e < VE; ++e)
+                  sum[i].v[e] += ok ? element<XT>(v[i * TU + j], e) : 0.f;
+              }
+        }
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+          const float inv = cnt[i] ? 1.0f / (float)cnt[i] : 0.f;
+          Cols<XT> self;
+#pragma unroll
+          for (int e = 0; e < VE; ++e) {
+            self.v[e] = element<XT>(own[i], e);
+            sum[i].v[e] *= inv;
+          }
+          if (!NARROW) {
+            shift_cols<XT>(self, past);
+            shift_cols<XT>(sum[i], past);
+          }
+          const int r = (q + i) * RG + lr;
+          if (r < RPW) {
+            float* d = A + (wv * RPW + r) * LD + c;
+#pragma unroll
+            for (int e = 0; e < VE; e += 4) {
+              *(f32x4*)(d + e) = f32x4{self.v[e], self.v[e + 1], self.v[e + 2], self.v[e + 3]};
+              *(f32x4*)(d + Sp::R * LD + e) =
+                  f32x4{sum[i].v[e], sum[i].v[e + 1], sum[i].v[e + 2], sum[i].v[e + 3]};
+            }
+          }
+        }
+      }
+      if (ps + 1 == npass) fetch_table(row0 + step);
+      __syncthreads();
+      // ---- product ----
+      const float* half = A + il * LD + 4 * g;
+      const int g0 = ps * (S / kGroup), g1 = min(g0 + S / kGroup, a.G);
+      for (int q4 = g0; q4 < g1; q4 += 4) {
+        f32x4 acc[Sp::RT][Sp::CT];
+#pragma unroll
+        for (int r = 0; r < Sp::RT; ++r)
+#pragma unroll
+          for (int t = 0; t < Sp::CT; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int qe = min(q4 + 4, g1);
+        for (int q = q4; q < qe; ++q) {
+          f32x4 w[2][Sp::CT];
+#pragma unroll
+          for (int sn = 0; sn < 2; ++sn)
+#pragma unroll
+            for (int t = 0; t < Sp::CT; ++t)
+              w[sn][t] = a.w[((int64_t)(q * 2 + sn) * NT + ct0 + t) * kWave + lane];
+#pragma unroll
+          for (int sn = 0; sn < 2; ++sn) {
+            f32x4 x[Sp::RT];
+#pragma unroll
+            for (int r = 0; r < Sp::RT; ++r)
+              x[r] = *(const f32x4*)(half + (sn * Sp::R + (rt0 + r) * 16) * LD + (q - g0) * kGroup);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+              for (int r = 0; r < Sp::RT; ++r)
+#pragma unroll
+                for (int t = 0; t < Sp::CT; ++t)
+                  acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r][e], w[sn][t][e], acc[r][t],
+                                                                   0, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < Sp::RT; ++r)
+#pragma unroll
+          for (int t = 0; t < Sp::CT; ++t) tot[r][t] += acc[r][t];
+      }
+      if (ps + 1 == npass) store_table(par ^ 1);
+      __syncthreads();
+    }
+    // D[i][j] of a tile sits in lane 16 * (i / 4) + j, element i % 4.
+#pragma unroll
+    for (int r = 0; r < Sp::RT; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int ri = (rt0 + r) * 16 + 4 * g + e;
+        const int64_t row = row0 + ri;
+        if (row >= n || pos[ri * pitch] < 0) continue;
+#pragma unroll
+        for (int t = 0; t < Sp::CT; ++t) {
+          const int cl = (ct0 + t) * 16 + il;
+          if (cl >= a.ncols) continue;
+          float y = tot[r][t][e] + (a.bias && cl < a.d_out ? a.bias[cl] : 0.f);
+          if (a.relu && y < 0.f) y = 0.f;
+          a.out[row * a.ncols + cl] = y;
+        }
+      }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// One layer of narrow outputs: projection of every input row, then the mean.
+// ---------------------------------------------------------------------------
+constexpr int kProjCols = 16;            // most output columns of this form
+
+struct ProjArgs {
+  const char* h;        // input rows of the level, back to back
+  int64_t h_stride;     // bytes
+  int32_t K;            // d_in
+  int32_t G;            // MFMA groups (packed)
+  const f32x4* w;       // packed weights, one column tile each of W_self and W_neigh
+  int32_t whole;        // all groups fit in LDS
+  float* z;             // [rows][32]: self columns, then neighbour columns
+  const int64_t* off;   // frontier_off at the input level
+  int32_t W;
+  int64_t rows_cap;
+};
+
+// Each wave owns 16 rows and loads them straight into registers, 16 bytes per
+// lane; bound by those reads and the 128 bytes written per row (1.56M rows of
+// 400 bytes in 190 us, 4.3 TB/s).
+template <int XT>
+__global__ void __launch_bounds__(kSageBlock, 8) k_sage_project(ProjArgs a) {
+  constexpr int VE = Cols<XT>::VE, ES = 16 / VE, MG = VE / 4;
+  constexpr int UL = 4;                                  // loads in flight per lane
+  constexpr int kGroupW = 2 * kWave;
+  extern __shared__ f32x4 swl[];
+  const int64_t nin = a.off[a.W] - a.off[0];
+  const int64_t n = nin < a.rows_cap ? nin : a.rows_cap;
+  const int lane = lane_id(), wv = (int)threadIdx.x / kWave;
+  const int g = lane >> 4, il = lane & 15;
+  if (a.whole) {
+    for (int i = threadIdx.x; i < a.G * kGroupW; i += kSageBlock) swl[i] = a.w[i];
+    __syncthreads();
+  }
+  const f32x4* wl = a.whole ? (const f32x4*)swl : a.w;
+  for (int64_t row0 = ((int64_t)blockIdx.x * 4 + wv) * 16; row0 < n;
+       row0 += (int64_t)gridDim.x * kTileRows) {
+    const int64_t r = row0 + il < n ? row0 + il : n - 1;
+    const char* rp = a.h + r * a.h_stride;
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    for (int s = 0; s * MG < a.G; s += UL) {
+      u32x4 raw[UL];
+#pragma unroll
+      for (int u = 0; u < UL; ++u) {
+        const int c = (s + u) * 4 * VE + VE * g;
+        if ((s + u) * MG < a.G) raw[u] = load16(rp + (c < a.K - VE ? c : a.K - VE) * ES);
+      }
+#pragma unroll
+      for (int u = 0; u < UL; ++u) {
+        if ((s + u) * MG >= a.G) break;
+        const int past = (s + u) * 4 * VE + VE * g + VE - a.K;
+        Cols<XT> v;
+#pragma unroll
+        for (int e = 0; e < VE; ++e) v.v[e] = element<XT>(raw[u], e);
+        if ((s + u + 1) * 4 * VE > a.K) shift_cols<XT>(v, past);
+#pragma unroll
+        for (int m = 0; m < MG; ++m) {
+          // columns 4 VE (s + u) + VE g + 4 m .. + 3, where the packed
+          // weights have them
+          const int cg = (s + u) * VE + MG * g + m;      // in fours of columns
+          const bool in = cg / 4 < a.G;
+#pragma unroll
+          for (int sn = 0; sn < 2; ++sn) {
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            const f32x4 b = in ? wl[(cg / 4 * 2 + sn) * kWave + cg % 4 * 16 + il] : zero;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              acc[sn] = __builtin_amdgcn_mfma_f32_16x16x4f32(v.v[m * 4 + e], b[e], acc[sn], 0, 0,
+                                                             0);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) {
+      const int64_t row = row0 + 4 * g + rr;
+      if (row >= n) continue;
+      a.z[row * 32 + il] = acc[0][rr];
+      a.z[row * 32 + 16 + il] = acc[1][rr];
+    }
+  }
+}
+
+// Sixteen lanes per output node, one column each; all of a node's projected
+// rows are in flight together (KMAX >= k) and summed in slot order.
+template <int KMAX>
+__global__ void __launch_bounds__(kSageBlock) k_sage_mean(LayerArgs a, const float* z,
+                                                          int32_t* status) {
+  const int64_t n = level_rows(a.off, a.W, a.rows_cap, a.out_cap, status);
+  const int lane = lane_id(), sl = lane & 15, gbase = lane & 48;
+  const int pitch = a.k + 1;
+  for (int64_t r = (int64_t)blockIdx.x * (kSageBlock / 16) + (threadIdx.x >> 4); r < n;
+       r += (int64_t)gridDim.x * (kSageBlock / 16)) {
+    const int32_t* row = a.table + r * pitch;
+    const int32_t e0 = sl < pitch ? row[sl] : -1;
+    const int32_t e1 = KMAX >= 16 && sl + 16 < pitch ? row[sl + 16] : -1;
+    const int32_t e2 = KMAX >= 32 && sl + 32 < pitch ? row[sl + 32] : -1;
+    const int32_t pv = __shfl(e0, gbase, kWave);
+    int32_t p[KMAX];
+    float v[KMAX];
+    int cnt = 0;
+#pragma unroll
+    for (int t = 0; t < KMAX; ++t) {
+      p[t] = __shfl(t + 1 < 16 ? e0 : (t + 1 < 32 ? e1 : e2), gbase + ((t + 1) & 15), kWave);
+      if (t >= a.k) p[t] = -1;
+      cnt += p[t] >= 0;
+    }
+    const float self = pv >= 0 ? z[(int64_t)pv * 32 + sl] : 0.f;
+#pragma unroll
+    for (int t = 0; t < KMAX; ++t) v[t] = p[t] >= 0 ? z[(int64_t)p[t] * 32 + 16 + sl] : 0.f;
+    float sum = 0.f;
+#pragma unroll
+    for (int t = 0; t < KMAX; ++t)
+      if (p[t] >= 0) sum += v[t];
+    if (pv < 0 || sl >= a.ncols) continue;
+    float y = self + sum * (cnt ? 1.0f / (float)cnt : 0.f) +
+              (a.bias && sl < a.d_out ? a.bias[sl] : 0.f);
+    if (a.relu && y < 0.f) y = 0.f;
+    a.out[r * a.ncols + sl] = y;
+  }
+}
+
+// Column tiles of a layer, rounded up to the compiled sizes.
+int col_tiles(int32_t d_out) {
+  const int need = (d_out + 15) / 16;
+  return need <= 4 ? need : (need <= 6 ? 6 : 8);
+}
+
+// Columns of a layer's output rows inside the call: padded with zeros to
+// whole MFMA groups, so that the next layer needs no care at row ends.
+int inner_cols(int32_t d_out) { return col_tiles(d_out) * 16; }
+
+int64_t packed_vecs(int32_t cols, int32_t d_out) {
+  return cdiv(cols, kGroup) * 2 * col_tiles(d_out) * kWave;
+}
+
+// A layer projects every input row first when reading the k + 1 input rows of
+// each output node would move more than twice as much: an input row read once
+// and 128 bytes written, and k + 1 lines of 128 bytes, against k + 1 rows with
+// about a line each for their unaligned ends.  A level holds about half as
+// many rows per output node as its hop draws, at most about four on dense
+// graphs.  The factor is for the rows that the caches serve again when they
+// are gathered.  Whole forward passes, projected / gathered first layers: 602
+// fp32 -> 16, ten neighbours, 286 / 385 us; 300 fp32 -> 12, fifteen, 146 / 281;
+// 100 fp32 -> 16, five, 342 / 347; 256 fp16 -> 16, ten, 141 / 104.
+bool use_projection(int32_t d_in, int32_t d_out, int64_t esz, int32_t k) {
+  if (d_out > kProjCols || d_in < 8) return false;
+  const int64_t row = d_in * esz;
+  const int64_t gathered = (k + 1) * (row + 112);
+  const int64_t projected = std::min<int64_t>((k + 1) * (row + 128) / 2, 4 * (row + 128)) +
+                            (k + 1) * 128;
+  return 2 * projected < gathered;
 }
 
 struct SageWs {
-  float* z;
   float* h[2];
-  int2* rank;
-  int32_t* csum;
+  float* z;
+  int32_t* table[GG_MAX_LAYERS];
+  int32_t* place[GG_MAX_LAYERS];
+  int32_t* rank;
+  f32x4* packed;
 };
 
 size_t sage_ws_layout(int64_t num_nodes, int32_t W, int64_t rows_cap, int32_t L,
                       const gg_sage_layer_t* layers, char* base, SageWs* out) {
-  int32_t dmax = 1, ntmax = 1;
+  int32_t dmax = 1;
+  int64_t vecs = 0;
   for (int32_t j = 0; j < L; ++j) {
-    dmax = std::max(dmax, layers[j].d_out);
-    ntmax = std::max(ntmax, ldz_tiles(layers[j].d_out));
+    if (j + 1 < L) dmax = std::max(dmax, inner_cols(layers[j].d_out));
+    vecs += packed_vecs(j ? inner_cols(layers[j - 1].d_out) : layers[j].d_in, layers[j].d_out);
   }
   const size_t r = (size_t)std::max<int64_t>(rows_cap, 1);
   const int64_t wpb = gg_bits_words(num_nodes);
-  const int64_t nch = wpb / kRankChunk;
   Carve cv{base, 0, ~(size_t)0};
-  float* z = cv.take<float>(r * (size_t)ntmax * 16);
-  float* h0 = cv.take<float>(r * (size_t)dmax);
-  float* h1 = cv.take<float>(r * (size_t)dmax);
-  int2* rank = cv.take<int2>((size_t)W * (size_t)wpb);
-  int32_t* csum = cv.take<int32_t>((size_t)W * (size_t)std::max<int64_t>(nch, 1));
-  if (out) *out = SageWs{z, {h0, h1}, rank, csum};
+  SageWs w;
+  for (int i = 0; i < 2; ++i) w.h[i] = cv.take<float>(r * (size_t)dmax);
+  w.z = cv.take<float>(layers[0].d_out <= kProjCols ? r * 32 : 0);
+  for (int32_t l = 0; l < L; ++l) w.table[l] = cv.take<int32_t>(r * kMaxPitch);
+  for (int32_t l = 1; l < L; ++l) w.place[l] = cv.take<int32_t>(r);
+  w.rank = cv.take<int32_t>((size_t)W * (size_t)(wpb / kRankWords));
+  w.packed = cv.take<f32x4>((size_t)vecs);
+  if (out) *out = w;
   return align_up(cv.used, 256);
 }
 
-template <int NT, int XT>
-void launch_project_v(bool vec, const ProjArgs& a, int grid, size_t lds, int32_t* status,
-                      hipStream_t stream) {
-  if (vec)
-    hipLaunchKernelGGL((k_sage_project<NT, XT, true>), dim3(grid), dim3(kSageBlock), lds, stream,
-                       a, status);
-  else
-    hipLaunchKernelGGL((k_sage_project<NT, XT, false>), dim3(grid), dim3(kSageBlock), lds, stream,
-                       a, status);
+template <int NT, int XT, int LR, bool NARROW = false>
+int launch_layer(LayerArgs& a, int64_t rows_bound, int32_t* status, hipStream_t stream) {
+  constexpr int R = Split<NT>::R;
+  const size_t lds =
+      (size_t)(2 * R * (LR * Cols<XT>::VE + 4) + 2 * R * (a.k + 1)) * sizeof(float);
+  // As many blocks as fit on the chip, each taking tile after tile.
+  const int64_t per_cu = std::min<int64_t>(4, (160 * 1024) / (int64_t)lds);
+  const int64_t grid = std::min<int64_t>(std::max<int64_t>(cdiv(rows_bound, R), 1),
+                                         256 * std::max<int64_t>(per_cu, 1));
+  hipLaunchKernelGGL((k_sage_layer<NT, XT, LR, NARROW>), dim3((unsigned)grid), dim3(kSageBlock),
+                     lds, stream, a, status);
+  GG_LAUNCH_CHECK("k_sage_layer");
+  return GG_OK;
 }
 
-template <int NT>
-void launch_project(int xt, bool vec, const ProjArgs& a, int grid, size_t lds, int32_t* status,
+// Lanes per source row: the row in one load of a few rows where it is narrow,
+// else the widest run whose operand tile leaves room for two blocks per CU.
+template <int NT, int XT>
+int launch_layer_u(LayerArgs& a, int64_t rows_bound, int32_t* status, hipStream_t stream) {
+  constexpr int VE = Cols<XT>::VE;
+  constexpr int kMin = NT <= 3 ? 4 : 8;          // at most as many rows per load as a wave gathers
+  if (a.K < VE) return launch_layer<NT, XT, kMin, true>(a, rows_bound, status, stream);
+  if constexpr (XT == GG_F32) {
+    if (a.K <= kMin * VE) return launch_layer<NT, XT, kMin>(a, rows_bound, status, stream);
+  }
+  if (NT <= 3 ? a.K <= 64 : a.K <= 128)
+    return launch_layer<NT, XT, (NT <= 3 ? 64 : 128) / VE>(a, rows_bound, status, stream);
+  return launch_layer<NT, XT, 128 / VE>(a, rows_bound, status, stream);
+}
+
+template <int XT>
+int launch_layer_nt(int nt, LayerArgs& a, int64_t rows_bound, int32_t* status,
                     hipStream_t stream) {
+  switch (nt) {
+    case 1: return launch_layer_u<1, XT>(a, rows_bound, status, stream);
+    case 2: return launch_layer_u<2, XT>(a, rows_bound, status, stream);
+    case 3: return launch_layer_u<3, XT>(a, rows_bound, status, stream);
+    case 4: return launch_layer_u<4, XT>(a, rows_bound, status, stream);
+    case 6: return launch_layer_u<6, XT>(a, rows_bound, status, stream);
+    default: return launch_layer_u<8, XT>(a, rows_bound, status, stream);
+  }
+}
+
+// The layer of output level lvl by projection: a's fields as for k_sage_layer.
+int launch_projected(LayerArgs& a, int xt, float* z, int64_t rows_cap, int32_t* status,
+                     hipStream_t stream) {
+  ProjArgs p;
+  p.h = a.h;
+  p.h_stride = a.h_stride;
+  p.K = a.K;
+  p.G = a.G;
+  p.w = a.w;
+  p.z = z;
+  p.off = a.off + a.W;
+  p.W = a.W;
+  p.rows_cap = rows_cap;
+  const int64_t wb = (int64_t)a.G * 2 * kWave * (int64_t)sizeof(f32x4);
+  p.whole = wb <= kWLdsBytes ? 1 : 0;
+  const int grid = (int)std::min<int64_t>(std::max<int64_t>(cdiv(rows_cap, kTileRows), 1), 2048);
+  const size_t lds = p.whole ? (size_t)wb : 0;
   if (xt == GG_F32)
-    launch_project_v<NT, GG_F32>(vec, a, grid, lds, status, stream);
+    hipLaunchKernelGGL(k_sage_project<GG_F32>, dim3(grid), dim3(kSageBlock), lds, stream, p);
   else
-    launch_project_v<NT, GG_F16>(vec, a, grid, lds, status, stream);
+    hipLaunchKernelGGL(k_sage_project<GG_F16>, dim3(grid), dim3(kSageBlock), lds, stream, p);
+  GG_LAUNCH_CHECK("k_sage_project");
+  const int mg = (int)std::min<int64_t>(std::max<int64_t>(cdiv(rows_cap, kSageBlock / 16), 1), 16384);
+  if (a.k <= 8)
+    hipLaunchKernelGGL(k_sage_mean<8>, dim3(mg), dim3(kSageBlock), 0, stream, a, z, status);
+  else if (a.k <= 16)
+    hipLaunchKernelGGL(k_sage_mean<16>, dim3(mg), dim3(kSageBlock), 0, stream, a, z, status);
+  else
+    hipLaunchKernelGGL(k_sage_mean<32>, dim3(mg), dim3(kSageBlock), 0, stream, a, z, status);
+  GG_LAUNCH_CHECK("k_sage_mean");
+  return GG_OK;
 }
 
 }  // namespace
@@ -451,91 +963,84 @@ extern "C" int gg_sage_forward(const gg_wsample_t* smp, int64_t num_nodes, int32
   const int64_t wpb = gg_bits_words(num_nodes);
   const int64_t nch = wpb / kRankChunk;
 
-  // ranks in the N_b bit sets
-  hipLaunchKernelGGL(k_rank_local, dim3((unsigned)nch, W), dim3(kSageBlock), 0, stream,
-                     smp->frontier_bits, wpb, nch, sw.rank, sw.csum);
-  GG_LAUNCH_CHECK("k_rank_local");
-  hipLaunchKernelGGL(k_rank_chunks, dim3(W), dim3(kSageBlock), 0, stream, sw.csum, nch);
-  GG_LAUNCH_CHECK("k_rank_chunks");
+  // Ranks in the N_b bit sets and packed weights.  A layer after the first
+  // contracts over its input's padded columns, whose weights are zero.
+  PackArgs pk;
+  pk.L = L;
+  pk.first[0] = 0;
+  int32_t cols[GG_MAX_LAYERS];
+  for (int32_t j = 0; j < L; ++j) {
+    const gg_sage_layer_t& ly = layers_h[j];
+    cols[j] = j ? inner_cols(layers_h[j - 1].d_out) : ly.d_in;
+    pk.w[j][0] = ly.w_self;
+    pk.w[j][1] = ly.w_neigh;
+    pk.d_in[j] = ly.d_in;
+    pk.d_out[j] = ly.d_out;
+    pk.nt[j] = col_tiles(ly.d_out);
+    pk.first[j + 1] = pk.first[j] + packed_vecs(cols[j], ly.d_out);
+  }
+  const int64_t pack_blocks = std::min<int64_t>(cdiv(pk.first[L], kSageBlock), 512);
+  hipLaunchKernelGGL(k_sage_prepare, dim3((unsigned)(nch * W + pack_blocks)), dim3(kSageBlock), 0,
+                     stream, smp->frontier_bits, (int32_t)nch, smp->frontier_ids,
+                     smp->frontier_off + (int64_t)L * W, W, (int2*)sw.rank, pk, sw.packed);
+  GG_LAUNCH_CHECK("k_sage_prepare");
+  RowsArgs ra;
+  ra.W = W;
+  ra.L = L;
+  for (int32_t l = 0; l < L; ++l) {
+    ra.k[l] = fanout_h[l];
+    ra.kmagic[l] = div_magic((uint32_t)fanout_h[l] + 1u);
+    ra.table[l] = sw.table[l];
+    ra.place[l] = l ? sw.place[l] : nullptr;
+  }
+  ra.fids = smp->frontier_ids;
+  ra.off = smp->frontier_off;
+  ra.nbr = smp->nbr_ids;
+  ra.noff = smp->nbr_off;
+  ra.bits = smp->frontier_bits;
+  ra.rank = sw.rank;
+  ra.wpb = wpb;
+  ra.rows_cap = rows_cap;
+  const int64_t rows_grid =
+      std::min<int64_t>(std::max<int64_t>(cdiv(rows_cap, kRowTile), 1), 1024);
+  if (L > 1) {
+    hipLaunchKernelGGL(k_sage_places, dim3((unsigned)rows_grid, (unsigned)(L - 1)),
+                       dim3(kSageBlock), 0, stream, ra);
+    GG_LAUNCH_CHECK("k_sage_places");
+  }
+  hipLaunchKernelGGL(k_sage_rows, dim3((unsigned)rows_grid, (unsigned)L), dim3(kSageBlock), 0,
+                     stream, ra, status_d);
+  GG_LAUNCH_CHECK("k_sage_rows");
 
-  const int proj_grid = (int)std::min<int64_t>(std::max<int64_t>(cdiv(rows_cap, kTileRows), 1), 8192);
-  const int agg_bx = (int)std::min<int64_t>(
-      std::max<int64_t>(cdiv(rows_cap, (int64_t)W * (kSageBlock / 16)), 1), 1024);
-  for (int32_t j = 1; j <= L; ++j) {
-    const gg_sage_layer_t& ly = layers_h[j - 1];
-    const int32_t lvl = L - j;
-    ProjArgs pa;
-    int xt;
-    if (j == 1) {
-      pa.h = (const char*)x_d;
-      pa.h_stride = x_stride;
-      xt = x_dtype;
-    } else {
-      pa.h = (const char*)sw.h[(j - 2) & 1];
-      pa.h_stride = (int64_t)layers_h[j - 2].d_out * 4;
-      xt = GG_F32;
-    }
-    const int vb = xt == GG_F32 ? 16 : 8;   // bytes of four elements
-    const bool vec = ((uintptr_t)pa.h % vb) == 0 && pa.h_stride % vb == 0;
-    const int nt = ldz_tiles(ly.d_out);
-    pa.K = ly.d_in;
-    pa.K16 = (ly.d_in + 15) / 16 * 16;
-    const int kc_max = kWLdsFloats / (nt * 16) / 16 * 16;
-    pa.kc = std::min(pa.K16, kc_max);
-    pa.d_out = ly.d_out;
-    pa.ldz = nt * 16;
-    pa.w_self = ly.w_self;
-    pa.w_neigh = ly.w_neigh;
-    pa.z = sw.z;
-    pa.off = smp->frontier_off;
-    pa.seg0 = (int64_t)(lvl + 1) * W;
-    pa.W = W;
-    pa.rows_cap = rows_cap;
-    const size_t lds = (size_t)pa.kc * nt * 16 * sizeof(float);
-    switch (nt) {
-      case 1: launch_project<1>(xt, vec, pa, proj_grid, lds, status_d, stream); break;
-      case 2: launch_project<2>(xt, vec, pa, proj_grid, lds, status_d, stream); break;
-      case 4: launch_project<4>(xt, vec, pa, proj_grid, lds, status_d, stream); break;
-      case 8: launch_project<8>(xt, vec, pa, proj_grid, lds, status_d, stream); break;
-      default: launch_project<16>(xt, vec, pa, proj_grid, lds, status_d, stream); break;
-    }
-    GG_LAUNCH_CHECK("k_sage_project");
-    AggArgs aa;
-    aa.fids = smp->frontier_ids;
-    aa.off = smp->frontier_off;
-    aa.nbr = smp->nbr_ids;
-    aa.noff = smp->nbr_off;
-    aa.W = W;
-    aa.lvl = lvl;
-    aa.k = fanout_h[lvl];
-    aa.z = sw.z;
-    aa.ldz = nt * 16;
-    aa.d_out = ly.d_out;
-    aa.bias = ly.bias;
-    aa.relu = ly.relu ? 1 : 0;
-    aa.z_cap = rows_cap;
-    if (j < L) {
-      aa.out = sw.h[(j - 1) & 1];
-      aa.out_cap = rows_cap;
-    } else {
-      aa.out = out_d;
-      aa.out_cap = out_rows_cap;
-    }
-    aa.use_rank = j == 1 ? 1 : 0;   // the first layer's input level is N_b
-    aa.rank = sw.rank;
-    aa.cpre = sw.csum;
-    aa.wpb = wpb;
-    aa.nch = nch;
-    if (aa.k <= 8)
-      hipLaunchKernelGGL(k_sage_aggregate<8>, dim3(agg_bx, W), dim3(kSageBlock), 0, stream, aa,
-                         status_d);
-    else if (aa.k <= 16)
-      hipLaunchKernelGGL(k_sage_aggregate<16>, dim3(agg_bx, W), dim3(kSageBlock), 0, stream, aa,
-                         status_d);
+  for (int32_t j = 0; j < L; ++j) {
+    const gg_sage_layer_t& ly = layers_h[j];
+    const int32_t lvl = L - 1 - j;
+    LayerArgs a;
+    a.h = j ? (const char*)sw.h[(j - 1) & 1] : (const char*)x_d;
+    a.h_stride = j ? (int64_t)cols[j] * 4 : x_stride;
+    a.K = cols[j];
+    a.G = (int32_t)cdiv(cols[j], kGroup);
+    a.w = sw.packed + pk.first[j];
+    a.k = fanout_h[lvl];
+    a.table = sw.table[lvl];
+    a.off = smp->frontier_off + (int64_t)lvl * W;
+    a.W = W;
+    a.bias = ly.bias;
+    a.d_out = ly.d_out;
+    a.relu = ly.relu ? 1 : 0;
+    a.ncols = j + 1 < L ? inner_cols(ly.d_out) : ly.d_out;
+    a.out = j + 1 < L ? sw.h[j & 1] : out_d;
+    a.rows_cap = rows_cap;
+    a.out_cap = j + 1 < L ? rows_cap : out_rows_cap;
+    const int xt = j == 0 ? x_dtype : GG_F32;
+    int rc;
+    if (j == 0 && use_projection(ly.d_in, ly.d_out, esz, a.k))
+      rc = launch_projected(a, xt, sw.z, rows_cap, status_d, stream);
+    else if (xt == GG_F16)
+      rc = launch_layer_nt<GG_F16>(pk.nt[j], a, rows_cap, status_d, stream);
     else
-      hipLaunchKernelGGL(k_sage_aggregate<32>, dim3(agg_bx, W), dim3(kSageBlock), 0, stream, aa,
-                         status_d);
-    GG_LAUNCH_CHECK("k_sage_aggregate");
+      rc = launch_layer_nt<GG_F32>(pk.nt[j], a, rows_cap, status_d, stream);
+    if (rc != GG_OK) return rc;
   }
   return GG_OK;
 }
