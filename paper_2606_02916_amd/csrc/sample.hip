@@ -54,6 +54,7 @@ struct SampleArgs {
   int32_t W, l, k;
   uint32_t key0, key1, epoch;
   uint8_t* bytemap;   // non-null: marks go to one byte per node (bytes per batch: 32 * wpb)
+  uint8_t* flags;     // non-null: marks also set their block's flag (use_flags)
   int32_t nomark;     // marks are left to k_mark_slices
 };
 
@@ -117,6 +118,28 @@ inline bool last_hop_slices(int64_t num_nodes, int32_t W, const Tune& tune) {
   return use_slices(num_nodes, tune) && W >= min_batches(use_bytemap(num_nodes, W, tune), tune);
 }
 
+// On large graphs a batch's set is mostly empty until the last hop (1,024
+// seeds, then some 3K and 20K entries among 111M nodes), and the compaction of
+// a level would read all of it twice.  One byte per block of 512 nodes (64
+// bytes of a set) then flags the blocks with a mark: each mark also stores its
+// block's flag (a plain byte store into 3.5 MB that stay in the caches), and
+// the counting and emitting passes read the flags and only the flagged blocks
+// (16 sets over 111M nodes, 222 MB: the two passes of levels 0, 1 and 2 take
+// 29, 35 and 58 us instead of about 190 each, those of the last, whose marks
+// touch 44% of the blocks, 118).  Taken where a window's sets are far larger than the caches and marks
+// are atomic ORs (too many LDS slices); smaller sets, whose passes are launch
+// latency, keep one block per chunk.  A tuning that turns off LDS slices and
+// the byte map takes it at any size.
+constexpr int64_t kFlagMinBytes = 32LL << 20;   // least bytes of a window's sets
+constexpr int kFlagWords = 16;                  // words per flag
+constexpr int kFlagChunks = 16;                 // chunks per emit block
+
+inline bool use_flags(int64_t num_nodes, int32_t W, const Tune& tune) {
+  if (use_slices(num_nodes, tune)) return false;
+  if (tune.mark_slices_max < 0 && tune.bytemap_max_bytes < 0) return true;
+  return (int64_t)W * gg_bits_words(num_nodes) * 4 >= kFlagMinBytes;
+}
+
 // Largest b in [0, 64) with off[b] <= x, for a table padded with INT64_MAX.
 __device__ __forceinline__ int find_batch(const int64_t* off, int64_t x) {
   int idx = 0;
@@ -127,9 +150,11 @@ __device__ __forceinline__ int find_batch(const int64_t* off, int64_t x) {
 }
 
 // Zeroes the window's bit sets (n4 16-byte words), the byte map (m4
-// 16-byte words, if any) and the per-level partial totals (nbtot).
+// 16-byte words, if any), the block flags (f4, if any) and the per-level
+// partial totals (nbtot).
 __global__ void __launch_bounds__(kBlock) k_zero_words(uint32_t* p, int64_t n4, uint8_t* map,
-                                                       int64_t m4, int32_t* btot, int32_t nbtot) {
+                                                       int64_t m4, uint8_t* flags, int64_t f4,
+                                                       int32_t* btot, int32_t nbtot) {
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < nbtot;
        t += (int64_t)gridDim.x * blockDim.x)
     btot[t] = 0;
@@ -142,6 +167,10 @@ __global__ void __launch_bounds__(kBlock) k_zero_words(uint32_t* p, int64_t n4, 
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m4;
        i += (int64_t)gridDim.x * blockDim.x)
     r[i] = z;
+  u32x4* f = (u32x4*)flags;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < f4;
+       i += (int64_t)gridDim.x * blockDim.x)
+    f[i] = z;
 }
 
 // Bits of four bytes that are each 0 or 1: byte i gives bit i.
@@ -155,7 +184,7 @@ __device__ __forceinline__ uint32_t pack16(u32x4 v) {
 
 __global__ void __launch_bounds__(kBlock) k_mark_seeds(const int32_t* seeds, SeedOff so, int32_t W,
                                                        uint32_t* bits, int64_t wpb, int64_t N,
-                                                       int32_t* status) {
+                                                       uint8_t* flags, int32_t* status) {
   const int64_t total = so.off[W];
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
        i += (int64_t)gridDim.x * blockDim.x) {
@@ -165,7 +194,9 @@ __global__ void __launch_bounds__(kBlock) k_mark_seeds(const int32_t* seeds, See
       set_status(status, GG_DEV_BAD_ID);
       continue;
     }
-    atomicOr(bits + (int64_t)b * wpb + (u >> 5), 1u << (u & 31));
+    const int64_t w = (int64_t)b * wpb + (u >> 5);
+    atomicOr(bits + w, 1u << (u & 31));
+    if (flags) flags[w / kFlagWords] = 1;
   }
 }
 
@@ -278,6 +309,37 @@ __global__ void __launch_bounds__(kBlock) k_bits_count(uint32_t* bits, int64_t w
   __syncthreads();
   if (threadIdx.x == 0) {
     const int32_t n = lds[0] + lds[1] + lds[2] + lds[3];
+    cnt[(int64_t)b * nch + c] = n;
+    if (n)
+      atomicAdd(tt.gtot + ((int64_t)b * tt.ngroups + c / kGroupChunks) * kTotLanes +
+                    (c & (kTotLanes - 1)),
+                n);
+  }
+}
+
+// As k_bits_count, reading flagged blocks only: one wavefront per chunk, two
+// blocks (1,024 nodes) per lane.
+__global__ void __launch_bounds__(kBlock) k_flag_count(const uint32_t* bits, int64_t wpb,
+                                                       const uint8_t* flags, int32_t nch,
+                                                       int32_t* cnt, Totals tt) {
+  const int c = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave, b = blockIdx.y;
+  if (c >= nch) return;
+  const int lane = lane_id();
+  const int64_t w0 = (int64_t)b * wpb + (int64_t)c * kChunkWords + lane * 2 * kFlagWords;
+  const uint32_t f = *(const uint16_t*)(flags + w0 / kFlagWords);
+  int n = 0;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    if ((f >> (8 * i)) & 1u) {
+      const u32x4* p = (const u32x4*)(bits + w0 + i * kFlagWords);
+#pragma unroll
+      for (int j = 0; j < kFlagWords / 4; ++j) {
+        const u32x4 x = p[j];
+        n += __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
+      }
+    }
+  n = wave_sum(n);
+  if (lane == 0) {
     cnt[(int64_t)b * nch + c] = n;
     if (n)
       atomicAdd(tt.gtot + ((int64_t)b * tt.ngroups + c / kGroupChunks) * kTotLanes +
@@ -455,25 +517,17 @@ __device__ __forceinline__ void block_sum3(int64_t (&v)[3], int64_t (*lds)[3]) {
   __syncthreads();
 }
 
-// Writes the ids of one chunk of one batch's bit set, ascending, at its
-// place in the level's list.  The place comes from the counts of the
-// previous launch: the totals of the batches before b plus the counts of
-// the chunks before c, summed by the block itself (no separate scan
-// launch).  Block (0, b) writes batch b's frontier and neighbour offsets;
-// block (0, 0) also the level's ends and capacity checks.
-__global__ void __launch_bounds__(kBlock) k_bits_emit(const uint32_t* bits, int64_t wpb,
-                                                      const int32_t* cnt, Totals tt,
-                                                      int32_t* ids, int64_t* frontier_off,
-                                                      int64_t* nbr_off, LevelState* ls,
-                                                      int64_t* need, int32_t* status,
-                                                      LevelArgs a) {
+// Where the ids of chunk c of batch b begin in the level's list, from the
+// counts of the previous launch: the totals of the batches before b plus the
+// counts of the chunks before c, summed by the block itself (no separate scan
+// launch).  Block (first chunk 0, b) writes batch b's frontier and neighbour
+// offsets; the first of all also the level's ends and capacity checks.
+__device__ __forceinline__ int64_t level_place(int c, int b, int nch, const int32_t* cnt,
+                                               const Totals& tt, int64_t* frontier_off,
+                                               int64_t* nbr_off, LevelState* ls, int64_t* need,
+                                               int32_t* status, const LevelArgs& a) {
   __shared__ int64_t lds3[kBlock / kWave][3];
-  __shared__ int32_t lds[kBlock / kWave];
   __shared__ int64_t s_off;
-  const int c = blockIdx.x, b = blockIdx.y, nch = gridDim.x;
-  const int64_t w0 = (int64_t)c * kChunkWords + threadIdx.x * kWordsPerThread;
-  const u32x4* p = (const u32x4*)(bits + (int64_t)b * wpb + w0);
-  const u32x4 x = p[0], y = p[1];      // in flight while the offsets are summed
   const int64_t raw_base = a.lv == 0 ? 0 : ls->fend[a.lv - 1];
   const int64_t raw_nbase = a.lv == 0 ? 0 : ls->nend[a.lv - 1];
   int64_t v[3] = {0, 0, 0};  // batches before b, all batches (block (0, 0)), chunks of b before c
@@ -481,15 +535,22 @@ __global__ void __launch_bounds__(kBlock) k_bits_emit(const uint32_t* bits, int6
     // a window of few chunks: every block sums the chunk counts before it
     const int64_t mine = (int64_t)b * nch;
     const int64_t upto = (b == 0 && c == 0) ? (int64_t)a.W * nch : mine + c;
-    for (int64_t t = threadIdx.x; t < upto; t += kBlock) {
-      const int64_t x = cnt[t];
-      v[1] += x;
-      if (t < mine) v[0] += x;
-      else if (t < mine + c) v[2] += x;
+    for (int64_t t0 = threadIdx.x; t0 < upto; t0 += 4 * kBlock) {
+      int32_t x[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] = t0 + j * kBlock < upto ? cnt[t0 + j * kBlock] : 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int64_t t = t0 + j * kBlock;
+        v[1] += x[j];
+        v[0] += t < mine ? x[j] : 0;
+        v[2] += t >= mine && t < mine + c ? x[j] : 0;
+      }
     }
   } else {
     const int64_t per_batch = (int64_t)tt.ngroups * kTotLanes;
     const int64_t upto = (b == 0 && c == 0) ? a.W * per_batch : b * per_batch;
+#pragma unroll 8
     for (int64_t t = threadIdx.x; t < upto; t += kBlock) {
       const int64_t x = tt.gtot[t];
       v[1] += x;
@@ -533,12 +594,30 @@ __global__ void __launch_bounds__(kBlock) k_bits_emit(const uint32_t* bits, int6
     }
   }
   __syncthreads();
+  return s_off;
+}
+
+// Writes the ids of one chunk of one batch's bit set, ascending, at its
+// place in the level's list.
+__global__ void __launch_bounds__(kBlock) k_bits_emit(const uint32_t* bits, int64_t wpb,
+                                                      const int32_t* cnt, Totals tt,
+                                                      int32_t* ids, int64_t* frontier_off,
+                                                      int64_t* nbr_off, LevelState* ls,
+                                                      int64_t* need, int32_t* status,
+                                                      LevelArgs a) {
+  __shared__ int32_t lds[kBlock / kWave];
+  const int c = blockIdx.x, b = blockIdx.y, nch = gridDim.x;
+  const int64_t w0 = (int64_t)c * kChunkWords + threadIdx.x * kWordsPerThread;
+  const u32x4* p = (const u32x4*)(bits + (int64_t)b * wpb + w0);
+  const u32x4 x = p[0], y = p[1];      // in flight while the offsets are summed
+  const int64_t off =
+      level_place(c, b, nch, cnt, tt, frontier_off, nbr_off, ls, need, status, a);
   const uint32_t w[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
   int n = 0;
 #pragma unroll
   for (int j = 0; j < 8; ++j) n += __popc(w[j]);
   int32_t tot;
-  int64_t pos = s_off + block_excl_scan<kBlock>(n, lds, &tot);
+  int64_t pos = off + block_excl_scan<kBlock>(n, lds, &tot);
   if (a.tile_runs) {
     // this thread's run of 8 words starts a tile every tile_runs runs
     const int64_t run = (int64_t)c * kBlock + threadIdx.x;
@@ -550,6 +629,87 @@ __global__ void __launch_bounds__(kBlock) k_bits_emit(const uint32_t* bits, int6
       if (pos < a.fcap) ids[pos] = (int32_t)((w0 + j) * 32 + (__ffs(m) - 1));
       ++pos;
     }
+  }
+}
+
+// As k_bits_emit, reading flagged blocks only: a block takes kFlagChunks
+// chunks of one batch (so that few blocks sum the totals before them), a
+// wavefront a quarter of them one after the other.
+__global__ void __launch_bounds__(kBlock) k_flag_emit(const uint32_t* bits, int64_t wpb,
+                                                      const uint8_t* flags, int32_t nch,
+                                                      const int32_t* cnt, Totals tt,
+                                                      int32_t* ids, int64_t* frontier_off,
+                                                      int64_t* nbr_off, LevelState* ls,
+                                                      int64_t* need, int32_t* status,
+                                                      LevelArgs a) {
+  static_assert(kGroupChunks % kFlagChunks == 0, "a block's chunks lie in one group");
+  constexpr int kPer = kFlagChunks / (kBlock / kWave);
+  const int c0 = blockIdx.x * kFlagChunks, b = blockIdx.y;
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+  const int first = c0 + wv * kPer;
+  uint32_t f[kPer];
+  int32_t mine[kPer];                  // counts of the wave's chunks
+  int64_t pos0 = 0;
+  for (int i = 0; i < wv * kPer; ++i)
+    if (c0 + i < nch) pos0 += cnt[(int64_t)b * nch + c0 + i];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int c = first + i;
+    f[i] = 0u;
+    mine[i] = 0;
+    if (c < nch) {
+      f[i] = *(const uint16_t*)(flags + ((int64_t)b * wpb + (int64_t)c * kChunkWords) / kFlagWords +
+                                2 * lane);
+      mine[i] = cnt[(int64_t)b * nch + c];
+    }
+  }
+  pos0 += level_place(c0, b, nch, cnt, tt, frontier_off, nbr_off, ls, need, status, a);
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int c = first + i;
+    if (c >= nch) break;
+    const int64_t w0 = (int64_t)c * kChunkWords + lane * 2 * kFlagWords;   // the lane's words
+    u32x4 x[2][kFlagWords / 4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const u32x4* p = (const u32x4*)(bits + (int64_t)b * wpb + w0 + h * kFlagWords);
+#pragma unroll
+      for (int j = 0; j < kFlagWords / 4; ++j) {
+        x[h][j] = u32x4{0u, 0u, 0u, 0u};
+        if ((f[i] >> (8 * h)) & 1u) x[h][j] = p[j];
+      }
+    }
+    int n[4];                          // bits of the lane's four runs of 8 words
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      n[r] = 0;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const u32x4 v = x[r / 2][r % 2 * 2 + j];
+        n[r] += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+      }
+    }
+    const int32_t all = n[0] + n[1] + n[2] + n[3];
+    int64_t pos = pos0 + wave_incl_scan(all) - all;
+    if (a.tile_runs) {
+      int64_t at = pos;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t run = (int64_t)c * kBlock + lane * 4 + r;
+        if (run % a.tile_runs == 0) a.tstart[(int64_t)b * a.ntiles + run / a.tile_runs] = at;
+        at += n[r];
+      }
+    }
+    if (f[i])
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < kFlagWords; ++j)
+          for (uint32_t m = x[h][j / 4][j % 4]; m; m &= m - 1u) {
+            if (pos < a.fcap) ids[pos] = (int32_t)((w0 + h * kFlagWords + j) * 32 + (__ffs(m) - 1));
+            ++pos;
+          }
+    pos0 += mine[i];
   }
 }
 
@@ -648,6 +808,7 @@ __device__ __forceinline__ void sample_one(const RowT* row_ptr, const int32_t* c
           a.bytemap[(int64_t)b * a.wpb * 32 + x] = 1;
         else
           atomicOr(brow + (x >> 5), 1u << (x & 31));
+        if (a.flags) a.flags[((int64_t)b * a.wpb + (x >> 5)) / kFlagWords] = 1;
       }
       out[i] = (i < cnt) ? x : -1;
     }
@@ -760,6 +921,7 @@ struct SampleWs {
   int64_t tot_level;  // entries of tot per level
   LevelState* lvl;
   uint8_t* map;       // the last hop's byte map (32 * wpb bytes per batch), or null
+  uint8_t* flags;     // block flags (wpb / kFlagWords bytes per batch), or null
   int64_t* tstart;    // node-tile table of one level: W * (wpb / 8) entries at most
 };
 
@@ -776,6 +938,9 @@ size_t sample_ws_layout(int64_t num_nodes, int32_t W, const Tune& tune, char* ba
   s.map = use_bytemap(num_nodes, W, tune) && !last_hop_slices(num_nodes, W, tune)
               ? cv.take<uint8_t>((size_t)W * (size_t)gg_bits_words(num_nodes) * 32)
               : nullptr;
+  s.flags = use_flags(num_nodes, W, tune)
+                ? cv.take<uint8_t>((size_t)W * (size_t)(gg_bits_words(num_nodes) / kFlagWords))
+                : nullptr;
   s.tstart = tune.sample_order != GG_SAMPLE_BATCH_ORDER
                  ? cv.take<int64_t>((size_t)W * (size_t)(gg_bits_words(num_nodes) / kWordsPerThread))
                  : nullptr;
@@ -915,27 +1080,33 @@ int sample_window_impl(const gg_csr_t* csr, const int32_t* seeds_d, const int64_
   // With few chunks in the window, level 0's counts come from k_seed_bits
   // and its emit sums them directly: one launch fewer.  Beside a running
   // gather even a small launch costs 7-12 us.
-  const bool seed_counts = max_batch <= kSeedBitsMaxBatch && (int64_t)W * nch <= kCntOnlyMaxChunks;
+  const bool seed_bits = max_batch <= kSeedBitsMaxBatch && !sw.flags;
+  const bool seed_counts = seed_bits && (int64_t)W * nch <= kCntOnlyMaxChunks;
   if (!do_bits) {
     // the last level only: its count unless the fold already made it, and
     // its emit
-  } else if (max_batch <= kSeedBitsMaxBatch) {
+  } else if (seed_bits) {
     hipLaunchKernelGGL(k_seed_bits, dim3((unsigned)nch, (unsigned)W), dim3(kBlock), 0, stream,
                        seeds_d, so, out->frontier_bits, wpb, N, sw.map, sw.tot,
                        (int32_t)((L + 1) * sw.tot_level), seed_counts ? sw.cnt : nullptr,
                        status_d);
     GG_LAUNCH_CHECK("k_seed_bits");
   } else {
+    // One chunk per block, every block reading its batch's seeds, suits few
+    // chunks; 27K of them (16 sets over 111M nodes) took 113 us, against 55
+    // for a streaming clear and 16K atomics.
     const int64_t map4 = sw.map ? W * wpb * 2 : 0;   // 32 bytes per word, 16 per store
+    const int64_t flag4 = sw.flags ? W * wpb / kFlagWords / 16 : 0;
     hipLaunchKernelGGL(k_zero_words,
                        dim3((unsigned)std::min<int64_t>(cdiv(W * wpb / 4, kBlock), 4096)),
                        dim3(kBlock), 0, stream, out->frontier_bits, W * wpb / 4, sw.map, map4,
-                       sw.tot, (int32_t)((L + 1) * sw.tot_level));
+                       sw.flags, flag4, sw.tot, (int32_t)((L + 1) * sw.tot_level));
     GG_LAUNCH_CHECK("k_zero_words");
     hipLaunchKernelGGL(k_mark_seeds,
-                       dim3((unsigned)std::min<int64_t>(cdiv(seed_off_h[W], kBlock), 4096)),
+                       dim3((unsigned)std::min<int64_t>(std::max<int64_t>(cdiv(seed_off_h[W], kBlock), 1),
+                                                       4096)),
                        dim3(kBlock), 0, stream, seeds_d, so, W, out->frontier_bits, wpb, N,
-                       status_d);
+                       sw.flags, status_d);
     GG_LAUNCH_CHECK("k_mark_seeds");
   }
   // Host bound on each level's entries, for the sampler's grid.
@@ -983,6 +1154,7 @@ int sample_window_impl(const gg_csr_t* csr, const int32_t* seeds_d, const int64_
       a.key1 = (uint32_t)(rng_seed >> 32);
       a.epoch = (uint32_t)epoch;
       a.bytemap = lv == L ? sw.map : nullptr;
+      a.flags = a.bytemap ? nullptr : sw.flags;
       a.nomark = lds_marks(lv) ? 1 : 0;
       const int64_t bnd = std::min<int64_t>(bound[lv - 1], out->frontier_cap);
       int rc = csr->row_ptr_bits == 64
@@ -996,6 +1168,7 @@ int sample_window_impl(const gg_csr_t* csr, const int32_t* seeds_d, const int64_
     tt.gtot = sw.tot + (int64_t)lv * sw.tot_level;
     tt.ngroups = sw.ngroups;
     const bool cnt_only = lv == 0 && seed_counts;
+    const bool flagged = sw.flags && !(last && sw.map);   // the byte map's draws set no flags
     // the last level's count folds the byte map, or makes the marks, which
     // the hot set needs, so it belongs to the bits part then; after atomic
     // marks it belongs to the compaction
@@ -1023,6 +1196,10 @@ int sample_window_impl(const gg_csr_t* csr, const int32_t* seeds_d, const int64_
         hipLaunchKernelGGL(k_mark_slices_256, mg, dim3(256), lds, stream, out->frontier_bits,
                            out->nbr_ids, out->nbr_off, sw.lvl, sw.cnt, tt, ma);
       GG_LAUNCH_CHECK("k_mark_slices");
+    } else if (!cnt_only && count_here && flagged) {
+      hipLaunchKernelGGL(k_flag_count, dim3((unsigned)cdiv(nch, kBlock / kWave), W), dim3(kBlock),
+                         0, stream, out->frontier_bits, wpb, sw.flags, nch, sw.cnt, tt);
+      GG_LAUNCH_CHECK("k_flag_count");
     } else if (!cnt_only && count_here) {
       hipLaunchKernelGGL(k_bits_count, dim3(nch, W), dim3(kBlock), 0, stream, out->frontier_bits,
                          wpb, lv == L ? sw.map : nullptr, sw.cnt, tt);
@@ -1046,6 +1223,14 @@ int sample_window_impl(const gg_csr_t* csr, const int32_t* seeds_d, const int64_
     // a fixed tile size is kept as is; otherwise tiles of up to 64 runs
     gmax_prev = tune.sample_tile_runs > 0 ? 1 : (la.tile_runs ? 64 / la.tile_runs : 1);
     if (last && !do_last) break;
+    if (flagged) {
+      hipLaunchKernelGGL(k_flag_emit, dim3((unsigned)cdiv(nch, kFlagChunks), W), dim3(kBlock), 0,
+                         stream, out->frontier_bits, wpb, sw.flags, nch, sw.cnt, tt,
+                         out->frontier_ids, out->frontier_off, out->nbr_off, sw.lvl, out->need,
+                         status_d, la);
+      GG_LAUNCH_CHECK("k_flag_emit");
+      continue;
+    }
     hipLaunchKernelGGL(k_bits_emit, dim3(nch, W), dim3(kBlock), 0, stream, out->frontier_bits, wpb,
                        sw.cnt, tt, out->frontier_ids, out->frontier_off, out->nbr_off, sw.lvl,
                        out->need, status_d, la);
