@@ -1,10 +1,9 @@
 // gg_bucket_by_owner: stable partition of the hot set by partition owner.
 //
-// Three passes over the ids: per-block owner histograms, one exclusive scan
-// over the (owner, block) counts in owner-major order, and a scatter in
-// which every wavefront ranks its 64 ids among equal owners with ballots
-// (one ballot per distinct owner present in the wave), so order is kept
-// inside each owner.
+// Two passes over the ids: per-block owner counts, and a scatter in which every
+// block places itself from all blocks' counts and every wavefront ranks its
+// ids among equal owners with ballots (one ballot per distinct owner present
+// in the wave), so order is kept inside each owner.
 //
 // Range partitions first try the identity: when owners never decrease along
 // the input (the ascending hot set always satisfies this), the input is
@@ -19,8 +18,22 @@
 namespace gg {
 namespace {
 
-constexpr int kIdsPerBlock = 4096;             // 16 per thread
-constexpr int kIdsPerWave = kIdsPerBlock / 4;  // 1024 = 16 groups of 64
+// The general path cuts the n ids into at most max_blocks(P) equal spans of
+// whole kSpanIds, one block each, sized on the device (the host knows the
+// capacity only).  Its second launch places a block from all blocks' counts, so
+// that they need no scan launch between the two: at most kMaxCounts of them,
+// 32 KB that stay in L2.
+constexpr int kSpanIds = 1024;                 // four groups of 64 per wave
+constexpr int kWaveGroups = kSpanIds / kBlock;
+constexpr int kMaxCounts = 8192;
+
+inline int max_blocks(int32_t P) { return std::max(kMaxCounts / P, 1); }
+
+// Ids per block for n ids and `blocks` blocks.
+__device__ __forceinline__ int64_t span_of(int64_t n, int blocks) {
+  const int64_t spans = (n + kSpanIds - 1) / kSpanIds;
+  return (spans + blocks - 1) / blocks * kSpanIds;
+}
 
 __device__ __forceinline__ int64_t bucket_n(const int64_t* hot_count, int64_t cap) {
   const int64_t n = hot_count[0];
@@ -28,12 +41,15 @@ __device__ __forceinline__ int64_t bucket_n(const int64_t* hot_count, int64_t ca
 }
 
 // Owner-order check and identity bucketing for range partitions.  A block
-// covers kRangeIds consecutive ids, four per thread, all loads issued
-// before any store.  It copies them, writes the owner_off entries of every
-// owner change it sees, and writes ok[blockIdx.x] = 1 when its ids were
-// valid and in owner order.
+// takes every gridDim.x-th run of kRangeIds consecutive ids, four per thread,
+// all loads issued before any store.  It copies them, writes the owner_off
+// entries of every owner change it sees, and writes ok[blockIdx.x] = 1 when its
+// ids were valid and in owner order.  The grid is capped: the capacity of a
+// 111M-node graph's hot set asks for 17K runs, of which a thousand hold ids
+// (34 us with a block each, 22 now, beside the window's other work).
 constexpr int kRangePer = 4;
 constexpr int kRangeIds = kBlock * kRangePer;
+constexpr int kRangeBlocks = 2048;
 
 __global__ void __launch_bounds__(kBlock) k_bucket_range(const int32_t* ids, const int64_t* hot_count,
                                                          int64_t cap, KPart part, int32_t* out,
@@ -48,36 +64,38 @@ __global__ void __launch_bounds__(kBlock) k_bucket_range(const int32_t* ids, con
   const int P = part.P;
   if (n == 0 && blockIdx.x == 0)
     for (int m = threadIdx.x; m <= P; m += blockDim.x) owner_off[m] = 0;
-  const int64_t i0 = (int64_t)blockIdx.x * kRangeIds + (int64_t)threadIdx.x * kRangePer;
-  int32_t v[kRangePer + 1];  // v[0] = the id before this thread's first
-#pragma unroll
-  for (int j = 0; j <= kRangePer; ++j) {
-    const int64_t i = i0 + j - 1;
-    v[j] = (i >= 0 && i < n) ? ids[i] : -1;
-  }
   int bad = 0, bad_id = 0;
-  int32_t op = -1;
-  if (i0 > 0 && i0 <= n) {
-    const int32_t up = v[0];
-    op = (up < 0 || (int64_t)up >= part.N) ? P : owner_of(part, s_start, up);
-  }
+  for (int64_t i0 = (int64_t)blockIdx.x * kRangeIds + (int64_t)threadIdx.x * kRangePer; i0 < n;
+       i0 += (int64_t)gridDim.x * kRangeIds) {
+    int32_t v[kRangePer + 1];  // v[0] = the id before this thread's first
 #pragma unroll
-  for (int j = 1; j <= kRangePer; ++j) {
-    const int64_t i = i0 + j - 1;
-    if (i >= n) break;
-    const int32_t u = v[j];
-    if (u < 0 || (int64_t)u >= part.N) {
-      bad = bad_id = 1;
-      op = P;
-      continue;
+    for (int j = 0; j <= kRangePer; ++j) {
+      const int64_t i = i0 + j - 1;
+      v[j] = (i >= 0 && i < n) ? ids[i] : -1;
     }
-    const int32_t o = owner_of(part, s_start, u);
-    if (op > o) bad = 1;
-    for (int32_t m = op + 1; m <= o; ++m) owner_off[m] = i;
-    if (i == n - 1)
-      for (int32_t m = o + 1; m <= P; ++m) owner_off[m] = n;
-    out[i] = u;
-    op = o;
+    int32_t op = -1;
+    if (i0 > 0 && i0 <= n) {
+      const int32_t up = v[0];
+      op = (up < 0 || (int64_t)up >= part.N) ? P : owner_of(part, s_start, up);
+    }
+#pragma unroll
+    for (int j = 1; j <= kRangePer; ++j) {
+      const int64_t i = i0 + j - 1;
+      if (i >= n) break;
+      const int32_t u = v[j];
+      if (u < 0 || (int64_t)u >= part.N) {
+        bad = bad_id = 1;
+        op = P;
+        continue;
+      }
+      const int32_t o = owner_of(part, s_start, u);
+      if (op > o) bad = 1;
+      for (int32_t m = op + 1; m <= o; ++m) owner_off[m] = i;
+      if (i == n - 1)
+        for (int32_t m = o + 1; m <= P; ++m) owner_off[m] = n;
+      out[i] = u;
+      op = o;
+    }
   }
   if (bad) atomicOr(&s_bad, bad_id ? 3 : 1);
   __syncthreads();
@@ -99,10 +117,11 @@ __device__ __forceinline__ bool range_done(const int32_t* ok, int32_t nok, int32
   return *s_flag != 0;
 }
 
+// The block's ids per owner: cnt[block][owner].
 __global__ void __launch_bounds__(kBlock) k_bucket_count(const int32_t* ids, const int64_t* hot_count,
                                                          int64_t cap, KPart part, int32_t* cnt,
-                                                         int32_t nblk, const int32_t* ok,
-                                                         int32_t nok, int32_t* status) {
+                                                         const int32_t* ok, int32_t nok,
+                                                         int32_t* status) {
   __shared__ int32_t s_flag;
   if (range_done(ok, nok, &s_flag)) return;
   __shared__ int32_t hist[GG_MAX_PARTS];
@@ -111,115 +130,133 @@ __global__ void __launch_bounds__(kBlock) k_bucket_count(const int32_t* ids, con
   for (int t = threadIdx.x; t <= GG_MAX_PARTS; t += blockDim.x) s_start[t] = part.start[t];
   __syncthreads();
   const int64_t n = bucket_n(hot_count, cap);
-  const int64_t i0 = (int64_t)blockIdx.x * kIdsPerBlock;
+  const int64_t span = span_of(n, gridDim.x);
+  const int64_t lo = blockIdx.x * span, hi = lo + span < n ? lo + span : n;
   int32_t st = 0;
-  for (int it = 0; it < kIdsPerBlock / kBlock; ++it) {
-    const int64_t i = i0 + it * kBlock + threadIdx.x;
-    bool valid = false;
-    int32_t m = 0;
-    if (i < n) {
-      const int32_t u = ids[i];
-      if (u < 0 || (int64_t)u >= part.N) {
+  for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += kSpanIds) {
+    int32_t u[kWaveGroups];
+#pragma unroll
+    for (int j = 0; j < kWaveGroups; ++j)
+      u[j] = i0 + j * kBlock < hi ? ids[i0 + j * kBlock] : INT32_MIN;
+#pragma unroll
+    for (int j = 0; j < kWaveGroups; ++j) {
+      if (u[j] >= 0 && (int64_t)u[j] < part.N)
+        atomicAdd(&hist[owner_of(part, s_start, u[j])], 1);
+      else if (i0 + j * kBlock < hi)
         st |= GG_DEV_BAD_ID;
-      } else {
-        valid = true;
-        m = owner_of(part, s_start, u);
-      }
     }
-    wave_hist_add(hist, valid, m);
   }
   if (st) set_status(status, st);
   __syncthreads();
-  for (int m = threadIdx.x; m < part.P; m += blockDim.x) cnt[(int64_t)m * nblk + blockIdx.x] = hist[m];
+  for (int m = threadIdx.x; m < part.P; m += blockDim.x)
+    cnt[(int64_t)blockIdx.x * part.P + m] = hist[m];
 }
 
-__global__ void __launch_bounds__(1024) k_bucket_scan(const int32_t* cnt, int64_t ncnt, int32_t nblk,
-                                                      int32_t P, int64_t* off, int64_t* owner_off,
-                                                      const int32_t* ok, int32_t nok) {
-  __shared__ int32_t s_flag;
-  if (range_done(ok, nok, &s_flag)) return;
-  __shared__ int64_t lds[16];
-  const int64_t total = block_scan_large(cnt, off, ncnt, 0, lds);
-  __syncthreads();
-  for (int m = threadIdx.x; m < P; m += blockDim.x) owner_off[m] = off[(int64_t)m * nblk];
-  if (threadIdx.x == 0) owner_off[P] = total;
-}
-
+// Every block sums the counts of all blocks per owner (and of the blocks
+// before it), which places its ids; block 0 writes owner_off.  Ids keep their
+// order inside each owner: a wave takes 256 consecutive ids, ranks each group
+// of 64 among equal owners by ballot (lane m keeps the wave's running count of
+// owner m), and the waves' counts order the waves.  Bound by launch latency
+// (105K ids, eight owners: 36 us with spans of 4,096 walked twice, and 19 + 5
+// for the count and scan launches before it; now 10 + 4).
 __global__ void __launch_bounds__(kBlock) k_bucket_scatter(const int32_t* ids, const int64_t* hot_count,
-                                                           int64_t cap, KPart part, const int64_t* off,
-                                                           int32_t nblk, const int32_t* ok,
-                                                           int32_t nok, int32_t* out) {
+                                                           int64_t cap, KPart part,
+                                                           const int32_t* cnt, int64_t* owner_off,
+                                                           const int32_t* ok, int32_t nok,
+                                                           int32_t* out) {
   __shared__ int32_t s_flag;
   if (range_done(ok, nok, &s_flag)) return;
-  __shared__ int32_t wcnt[4][GG_MAX_PARTS];
-  __shared__ int64_t wbase[4][GG_MAX_PARTS];
+  constexpr int kWaves = kBlock / kWave;
+  __shared__ int32_t s_tot[GG_MAX_PARTS], s_before[GG_MAX_PARTS];
+  __shared__ int32_t s_base[GG_MAX_PARTS];     // next output position of each owner
+  __shared__ int32_t s_wave[kWaves][GG_MAX_PARTS];
   __shared__ int64_t s_start[GG_MAX_PARTS + 1];
-  const int w = threadIdx.x / kWave, lane = lane_id();
-  for (int t = threadIdx.x; t < 4 * GG_MAX_PARTS; t += blockDim.x) (&wcnt[0][0])[t] = 0;
+  const int P = part.P, w = threadIdx.x / kWave, lane = lane_id();
+  for (int t = threadIdx.x; t < GG_MAX_PARTS; t += blockDim.x) s_tot[t] = s_before[t] = 0;
   for (int t = threadIdx.x; t <= GG_MAX_PARTS; t += blockDim.x) s_start[t] = part.start[t];
   __syncthreads();
   const int64_t n = bucket_n(hot_count, cap);
-  const int64_t i0 = (int64_t)blockIdx.x * kIdsPerBlock + (int64_t)w * kIdsPerWave;
-  // Per-wave owner counts.
-  for (int g = 0; g < kIdsPerWave / kWave; ++g) {
-    const int64_t i = i0 + g * kWave + lane;
-    bool valid = false;
-    int32_t m = 0;
-    if (i < n) {
-      const int32_t u = ids[i];
-      if (u >= 0 && (int64_t)u < part.N) {
-        valid = true;
-        m = owner_of(part, s_start, u);
+  const int64_t span = span_of(n, gridDim.x);
+  const int64_t lo = blockIdx.x * span, hi = lo + span < n ? lo + span : n;
+  // threads in whole rows of P counts: each keeps to one owner
+  const int rows = kBlock / P;
+  if ((int)threadIdx.x < rows * P) {
+    const int nb = span > 0 ? (int)((n + span - 1) / span) : 0;   // blocks with ids
+    const int m = threadIdx.x % P;
+    int32_t tot = 0, before = 0;
+#pragma unroll 8
+    for (int x = threadIdx.x / P; x < nb; x += rows) {
+      const int32_t c = cnt[(int64_t)x * P + m];
+      tot += c;
+      before += x < (int)blockIdx.x ? c : 0;
+    }
+    if (tot) atomicAdd(&s_tot[m], tot);
+    if (before) atomicAdd(&s_before[m], before);
+  }
+  __syncthreads();
+  if (w == 0) {
+    const int32_t t = lane < P ? s_tot[lane] : 0;
+    const int32_t first = wave_incl_scan(t) - t;
+    if (lane < P) {
+      s_base[lane] = first + s_before[lane];
+      if (blockIdx.x == 0) {
+        owner_off[lane] = first;
+        if (lane == P - 1) owner_off[P] = first + t;
       }
     }
-    wave_hist_add(wcnt[w], valid, m);
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < 4 * part.P; t += blockDim.x) {
-    const int ww = t / part.P, m = t - ww * part.P;
-    int64_t b = off[(int64_t)m * nblk + blockIdx.x];
-    for (int v = 0; v < ww; ++v) b += wcnt[v][m];
-    wbase[ww][m] = b;
-  }
-  __syncthreads();
-  // Ordered scatter: groups of 64 in id order, ranks by ballot per owner.
-  // Lane m keeps the running output position of owner m.
-  int64_t my_base = lane < part.P ? wbase[w][lane] : 0;
-  for (int g = 0; g < kIdsPerWave / kWave; ++g) {
-    const int64_t i = i0 + g * kWave + lane;
-    int32_t u = -1, o = -1;
-    bool valid = false;
-    if (i < n) {
-      u = ids[i];
-      valid = u >= 0 && (int64_t)u < part.N;
-      if (valid) o = owner_of(part, s_start, u);
+  for (int64_t i0 = lo; i0 < hi; i0 += kSpanIds) {
+    const int64_t iw = i0 + w * (kSpanIds / kWaves) + lane;
+    int32_t u[kWaveGroups], o[kWaveGroups], rank[kWaveGroups];
+    int32_t mine = 0;                          // lane m: the wave's ids of owner m so far
+#pragma unroll
+    for (int g = 0; g < kWaveGroups; ++g) u[g] = iw + g * kWave < hi ? ids[iw + g * kWave] : -1;
+#pragma unroll
+    for (int g = 0; g < kWaveGroups; ++g) {
+      const bool valid = u[g] >= 0 && (int64_t)u[g] < part.N;
+      o[g] = valid ? owner_of(part, s_start, u[g]) : -1;
+      rank[g] = 0;
+      for (uint64_t active = __ballot(valid); active;) {
+        const int leader = __ffsll((unsigned long long)active) - 1;
+        const int32_t ol = __shfl(o[g], leader, kWave);
+        const uint64_t mm = __ballot(valid && o[g] == ol);
+        const int32_t before = __shfl(mine, ol, kWave);
+        if (o[g] == ol) rank[g] = before + lanes_below(mm);
+        if (lane == ol) mine += (int32_t)__popcll(mm);
+        active &= ~mm;
+      }
     }
-    uint64_t active = __ballot(valid);
-    while (active) {
-      const int leader = __ffsll((unsigned long long)active) - 1;
-      const int32_t ol = __shfl(o, leader, kWave);
-      const uint64_t mm = __ballot(valid && o == ol);
-      const int64_t b = __shfl(my_base, ol, kWave);
-      if (valid && o == ol) out[b + lanes_below(mm)] = u;
-      if (lane == ol) my_base += __popcll(mm);
-      active &= ~mm;
-    }
+    if (lane < P) s_wave[w][lane] = mine;
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < kWaveGroups; ++g)
+      if (o[g] >= 0) {
+        int32_t at = s_base[o[g]] + rank[g];
+        for (int v = 0; v < w; ++v) at += s_wave[v][o[g]];
+        out[at] = u[g];
+      }
+    __syncthreads();
+    if ((int)threadIdx.x < P)
+      for (int v = 0; v < kWaves; ++v) s_base[threadIdx.x] += s_wave[v][threadIdx.x];
+    __syncthreads();
   }
 }
 
 struct BucketWs {
   int32_t* cnt;
-  int64_t* off;
   int32_t* ok;
 };
 
+int bucket_blocks(int64_t cap, int32_t P) {
+  return (int)std::min<int64_t>(std::max<int64_t>(1, cdiv(cap, kSpanIds)), max_blocks(P));
+}
+
 size_t bucket_ws_layout(int64_t cap, int32_t P, char* base, BucketWs* out) {
-  const int64_t nblk = std::max<int64_t>(1, cdiv(cap, kIdsPerBlock));
   Carve cv{base, 0, ~(size_t)0};
   BucketWs b;
-  b.cnt = cv.take<int32_t>((size_t)(nblk * P));
-  b.off = cv.take<int64_t>((size_t)(nblk * P));
-  b.ok = cv.take<int32_t>((size_t)std::max<int64_t>(1, cdiv(cap, kRangeIds)));
+  b.cnt = cv.take<int32_t>((size_t)bucket_blocks(cap, P) * (size_t)P);
+  b.ok = cv.take<int32_t>((size_t)kRangeBlocks);
   if (out) *out = b;
   return align_up(cv.used, 256);
 }
@@ -247,8 +284,7 @@ extern "C" int gg_bucket_by_owner(const int32_t* hot_ids_d, const int64_t* hot_c
   BucketWs bw;
   const size_t need_ws = bucket_ws_layout(cap, kp.P, (char*)ws, &bw);
   GG_REQUIRE(ws && ws_bytes >= need_ws, "workspace of %zu bytes < %zu", ws_bytes, need_ws);
-  const int32_t nblk = (int32_t)std::max<int64_t>(1, cdiv(cap, kIdsPerBlock));
-  const int32_t nrange = (int32_t)std::max<int64_t>(1, cdiv(cap, kRangeIds));
+  const int32_t nrange = (int32_t)std::min<int64_t>(std::max<int64_t>(1, cdiv(cap, kRangeIds)), kRangeBlocks);
   const int32_t* ok = nullptr;
   if (kp.kind == GG_PART_RANGE) {
     // Owner-ordered input under ranges is its own bucketing.  When the
@@ -262,14 +298,12 @@ extern "C" int gg_bucket_by_owner(const int32_t* hot_ids_d, const int64_t* hot_c
     if (trusted) return GG_OK;
     ok = bw.ok;
   }
-  hipLaunchKernelGGL(k_bucket_count, dim3(nblk), dim3(kBlock), 0, stream, hot_ids_d, hot_count_d, cap,
-                     kp, bw.cnt, nblk, ok, nrange, status_d);
+  const int grid = bucket_blocks(cap, kp.P);
+  hipLaunchKernelGGL(k_bucket_count, dim3(grid), dim3(kBlock), 0, stream, hot_ids_d, hot_count_d,
+                     cap, kp, bw.cnt, ok, nrange, status_d);
   GG_LAUNCH_CHECK("k_bucket_count");
-  hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(1024), 0, stream, bw.cnt, (int64_t)nblk * kp.P,
-                     nblk, kp.P, bw.off, owner_off_d, ok, nrange);
-  GG_LAUNCH_CHECK("k_bucket_scan");
-  hipLaunchKernelGGL(k_bucket_scatter, dim3(nblk), dim3(kBlock), 0, stream, hot_ids_d, hot_count_d,
-                     cap, kp, bw.off, nblk, ok, nrange, bucket_ids_d);
+  hipLaunchKernelGGL(k_bucket_scatter, dim3(grid), dim3(kBlock), 0, stream, hot_ids_d, hot_count_d,
+                     cap, kp, bw.cnt, owner_off_d, ok, nrange, bucket_ids_d);
   GG_LAUNCH_CHECK("k_bucket_scatter");
   return GG_OK;
 }

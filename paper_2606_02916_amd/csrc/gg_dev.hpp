@@ -146,38 +146,6 @@ __device__ __forceinline__ T block_excl_scan(T v, T* lds, T* total) {
   return base + inc - v;
 }
 
-// Exclusive scan of in[0..n) into out[0..n) plus `base`, by one block of
-// NT threads, 16 consecutive items per thread per tile; lds holds NT/64
-// entries.  Returns the sum.
-template <int NT = 1024>
-__device__ __forceinline__ int64_t block_scan_large(const int32_t* in, int64_t* out, int64_t n,
-                                                    int64_t base, int64_t* lds16) {
-  constexpr int IT = 16;
-  int64_t carry = base;
-  for (int64_t t0 = 0; t0 < n; t0 += (int64_t)NT * IT) {
-    int32_t loc[IT];
-    int64_t sum = 0;
-    const int64_t i0 = t0 + (int64_t)threadIdx.x * IT;
-#pragma unroll
-    for (int j = 0; j < IT; ++j) {
-      const int64_t i = i0 + j;
-      loc[j] = i < n ? in[i] : 0;
-      sum += loc[j];
-    }
-    int64_t tot;
-    const int64_t ex = block_excl_scan<NT>(sum, lds16, &tot);
-    int64_t run = carry + ex;
-#pragma unroll
-    for (int j = 0; j < IT; ++j) {
-      const int64_t i = i0 + j;
-      if (i < n) out[i] = run;
-      run += loc[j];
-    }
-    carry += tot;
-  }
-  return carry - base;
-}
-
 // hist[key] += number of active lanes with `valid` and that key: one LDS
 // atomic per distinct key present in the wave.  Call from every active lane.
 __device__ __forceinline__ void wave_hist_add(int32_t* hist, bool valid, int32_t key) {
