@@ -177,13 +177,7 @@ __global__ void __launch_bounds__(kBlock) k_gather_stats(const int64_t* bounds, 
   const int s = blockIdx.x;
   for (int t = threadIdx.x; t < 2 + GG_MAX_PARTS; t += blockDim.x) s_sum[t] = 0;
   __syncthreads();
-  for (int j = 0; j < a.nstat; ++j) {
-    int32_t v = 0;
-    for (int x = threadIdx.x; x < bx; x += blockDim.x)
-      v += blk_stat[((int64_t)s * bx + x) * a.nstat + j];
-    v = wave_sum(v);
-    if (lane_id() == 0 && v) atomicAdd(&s_sum[j], v);
-  }
+  sum_columns(blk_stat + (int64_t)s * bx * a.nstat, bx, a.nstat, s_sum);
   __syncthreads();
   gg_gather_stats_t* o = stats + s;
   if (threadIdx.x < GG_MAX_PARTS) {

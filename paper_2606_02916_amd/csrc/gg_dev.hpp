@@ -159,6 +159,19 @@ __device__ __forceinline__ void wave_hist_add(int32_t* hist, bool valid, int32_t
   }
 }
 
+// sum[j] += the entries j of the n rows of `cols` (at most kBlock) counters at
+// p, by one block: the rows lie back to back, and a thread keeps to one
+// column, so that all of its loads are in flight together.
+__device__ __forceinline__ void sum_columns(const int32_t* p, int n, int cols, int32_t* sum) {
+  const int rows = kBlock / cols;
+  if ((int)threadIdx.x >= rows * cols) return;
+  const int j = threadIdx.x % cols;
+  int32_t v = 0;
+#pragma unroll 8
+  for (int x = threadIdx.x / cols; x < n; x += rows) v += p[(int64_t)x * cols + j];
+  if (v) atomicAdd(&sum[j], v);
+}
+
 // ---------------------------------------------------------------------------
 // Row copy engine.  A wavefront copies up to 64 rows: lane r supplies the
 // source of row r (nullptr = skip that row) and the rows land at

@@ -102,8 +102,9 @@ __global__ void __launch_bounds__(kBlock) k_slot_reset(const int32_t* prev, cons
 
 // Statistics of the call: per-owner requests, rows and bytes and the
 // rebuild delta.  Their inputs (owner_off, the delta counts of
-// k_stage_delta) are complete before k_stage_rows starts, so its block 0
-// computes them.
+// k_stage_delta) are complete before k_stage_rows starts, so a last block of
+// its own computes them there (a block that did so in front of its rows made
+// a small staging wait for it).
 struct StageStatsArgs {
   const int64_t* prev_count;
   const int32_t* dcnt;
@@ -127,12 +128,7 @@ __device__ void stage_stats(const int64_t* owner_off, const KPart& part, const S
   __shared__ int32_t s_delta[GG_MAX_PARTS];
   for (int t = threadIdx.x; t < GG_MAX_PARTS; t += blockDim.x) s_delta[t] = 0;
   __syncthreads();
-  for (int m = 0; m < part.P; ++m) {
-    int32_t v = 0;
-    for (int x = threadIdx.x; x < nblk_delta; x += blockDim.x) v += dcnt[(int64_t)x * part.P + m];
-    v = wave_sum(v);
-    if (lane_id() == 0 && v) atomicAdd(&s_delta[m], v);
-  }
+  sum_columns(dcnt, nblk_delta, part.P, s_delta);
   __syncthreads();
   const int64_t n = sa.nfree ? inplace_n(owner_off, part.P, a) : stage_n(owner_off, part.P, a);
   // slots the delta can take (in place): free ones below the previous
@@ -187,7 +183,11 @@ __global__ void __launch_bounds__(kBlock) k_stage_rows(const int32_t* bucket, co
                                                        char* cache, int32_t* slot_of,
                                                        const char* src_cache, const int32_t* old_slot,
                                                        StageStatsArgs sa, int32_t* status) {
-  if (blockIdx.x == 0) stage_stats(owner_off, part, a, feat.row_bytes, sa, status);
+  const int nblocks = gridDim.x - 1;
+  if ((int)blockIdx.x == nblocks) {
+    stage_stats(owner_off, part, a, feat.row_bytes, sa, status);
+    return;
+  }
   __shared__ int64_t s_start[GG_MAX_PARTS + 1];
   for (int t = threadIdx.x; t <= GG_MAX_PARTS; t += blockDim.x) s_start[t] = part.start[t];
   __syncthreads();
@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(kBlock) k_stage_rows(const int32_t* bucket, co
   const int lane = lane_id();
   int32_t st = 0;
   for (int64_t tile = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave; tile < ntiles;
-       tile += (int64_t)gridDim.x * (kBlock / kWave)) {
+       tile += (int64_t)nblocks * (kBlock / kWave)) {
     const int64_t s0 = tile * a.tile;
     const int64_t s = s0 + lane;
     const char* src = nullptr;
@@ -234,7 +234,7 @@ void launch_stage_rows(int grid, hipStream_t stream, const int32_t* bucket,
                        const int64_t* owner_off, const KPart& kp, const KFeat& kf,
                        const StageArgs& a, char* cache, int32_t* slot_of, const char* src_cache,
                        const int32_t* old_slot, const StageStatsArgs& sa, int32_t* status) {
-  hipLaunchKernelGGL((k_stage_rows<VB, false>), dim3(grid), dim3(kBlock), 0, stream, bucket,
+  hipLaunchKernelGGL((k_stage_rows<VB, false>), dim3(grid + 1), dim3(kBlock), 0, stream, bucket,
                      owner_off, kp, kf, a, cache, slot_of, src_cache, old_slot, sa, status);
 }
 
@@ -518,7 +518,11 @@ __global__ void __launch_bounds__(kBlock) k_inplace_rows(
     const int32_t* btot, const int64_t* bpre, int32_t gp, const int32_t* freel,
     const int64_t* nfree_p, const uint8_t* occ_prev, uint8_t* occ, StageStatsArgs sa,
     int32_t* status) {
-  if (blockIdx.x == 0) stage_stats(owner_off, part, a, feat.row_bytes, sa, status);
+  const int nblocks = gridDim.x - 1;
+  if ((int)blockIdx.x == nblocks) {
+    stage_stats(owner_off, part, a, feat.row_bytes, sa, status);
+    return;
+  }
   __shared__ int64_t s_start[GG_MAX_PARTS + 1];
   for (int t = threadIdx.x; t <= GG_MAX_PARTS; t += blockDim.x) s_start[t] = part.start[t];
   __syncthreads();
@@ -535,7 +539,7 @@ __global__ void __launch_bounds__(kBlock) k_inplace_rows(
   const int lane = lane_id();
   int32_t st = 0;
   for (int64_t tile = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave; tile < ntiles;
-       tile += (int64_t)gridDim.x * (kBlock / kWave)) {
+       tile += (int64_t)nblocks * (kBlock / kWave)) {
     const int64_t s0 = tile * a.tile;
     const int64_t s = s0 + lane;
     const bool live = lane < a.tile && s < n;
@@ -763,12 +767,12 @@ extern "C" int gg_stage_inplace(const int32_t* bucket_ids_d, const int64_t* owne
   sa.has_src = 1;
   // Cache rows are stored with ordinary stores: the gathers read them next.
   if (v16)
-    hipLaunchKernelGGL((k_inplace_rows<16, false>), dim3(grid), dim3(kBlock), 0, stream,
+    hipLaunchKernelGGL((k_inplace_rows<16, false>), dim3(grid + 1), dim3(kBlock), 0, stream,
                        bucket_ids_d, owner_off_d, kp, kf, a, (char*)cache_d, slot_of_d,
                        w.old_slot, w.dr, w.btot, w.bpre, gridp, w.freel, w.nfree, occ_prev_d,
                        occ_d, sa, status_d);
   else
-    hipLaunchKernelGGL((k_inplace_rows<4, false>), dim3(grid), dim3(kBlock), 0, stream,
+    hipLaunchKernelGGL((k_inplace_rows<4, false>), dim3(grid + 1), dim3(kBlock), 0, stream,
                        bucket_ids_d, owner_off_d, kp, kf, a, (char*)cache_d, slot_of_d,
                        w.old_slot, w.dr, w.btot, w.bpre, gridp, w.freel, w.nfree, occ_prev_d,
                        occ_d, sa, status_d);
