@@ -598,37 +598,71 @@ __device__ __forceinline__ int64_t level_place(int c, int b, int nch, const int3
 }
 
 // Writes the ids of one chunk of one batch's bit set, ascending, at its
-// place in the level's list.
+// place in the level's list.  A wave takes 512 consecutive words in eight
+// rounds of 64, one word per lane, so that the lanes' ids of a round lie side
+// by side in the list and their stores fall into a few lines (with eight
+// consecutive words per lane every store of a wave touched up to 64: beside a
+// gather, the dense lists of the 233K-node graph, 33K ids per batch, took 15.9
+// us a level, now 11.3).  The rounds' counts are
+// scanned two to a register.
 __global__ void __launch_bounds__(kBlock) k_bits_emit(const uint32_t* bits, int64_t wpb,
                                                       const int32_t* cnt, Totals tt,
                                                       int32_t* ids, int64_t* frontier_off,
                                                       int64_t* nbr_off, LevelState* ls,
                                                       int64_t* need, int32_t* status,
                                                       LevelArgs a) {
-  __shared__ int32_t lds[kBlock / kWave];
+  constexpr int kRounds = kWordsPerThread;
+  static_assert(kWave * 32 < 1 << 16, "a round's counts fit in 16 bits");
+  __shared__ int32_t s_wave[kBlock / kWave];
   const int c = blockIdx.x, b = blockIdx.y, nch = gridDim.x;
-  const int64_t w0 = (int64_t)c * kChunkWords + threadIdx.x * kWordsPerThread;
-  const u32x4* p = (const u32x4*)(bits + (int64_t)b * wpb + w0);
-  const u32x4 x = p[0], y = p[1];      // in flight while the offsets are summed
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+  const int32_t w0 = c * kChunkWords + wv * (kRounds * kWave) + lane;   // the first round's word
+  const uint32_t* p = bits + (int64_t)b * wpb + w0;
+  uint32_t w[kRounds];
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) w[r] = p[r * kWave];   // in flight while the offsets are summed
   const int64_t off =
       level_place(c, b, nch, cnt, tt, frontier_off, nbr_off, ls, need, status, a);
-  const uint32_t w[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-  int n = 0;
+  uint32_t own[kRounds / 2], inc[kRounds / 2];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) n += __popc(w[j]);
-  int32_t tot;
-  int64_t pos = off + block_excl_scan<kBlock>(n, lds, &tot);
-  if (a.tile_runs) {
-    // this thread's run of 8 words starts a tile every tile_runs runs
-    const int64_t run = (int64_t)c * kBlock + threadIdx.x;
-    if (run % a.tile_runs == 0) a.tstart[(int64_t)b * a.ntiles + run / a.tile_runs] = pos;
+  for (int q = 0; q < kRounds / 2; ++q)
+    inc[q] = own[q] = (uint32_t)__popc(w[2 * q]) | ((uint32_t)__popc(w[2 * q + 1]) << 16);
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1)
+#pragma unroll
+    for (int q = 0; q < kRounds / 2; ++q) {
+      const uint32_t t = __shfl_up(inc[q], o, kWave);
+      if (lane >= o) inc[q] += t;
+    }
+  int32_t first[kRounds];              // the lane's place in the wave's list, by round
+  int32_t run = 0;
+#pragma unroll
+  for (int q = 0; q < kRounds / 2; ++q) {
+    const uint32_t ex = inc[q] - own[q];
+    const uint32_t tot = __shfl(inc[q], kWave - 1, kWave);
+    first[2 * q] = run + (int32_t)(ex & 0xFFFFu);
+    run += (int32_t)(tot & 0xFFFFu);
+    first[2 * q + 1] = run + (int32_t)(ex >> 16);
+    run += (int32_t)(tot >> 16);
+  }
+  if (lane == 0) s_wave[wv] = run;
+  __syncthreads();
+  int64_t base = off;
+  for (int v = 0; v < wv; ++v) base += s_wave[v];
+  if (a.tile_runs && lane % kWordsPerThread == 0) {
+    // a run is 8 words; every tile_runs runs start a tile
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      const int64_t at = (w0 + r * kWave) / kWordsPerThread;
+      if (at % a.tile_runs == 0) a.tstart[(int64_t)b * a.ntiles + at / a.tile_runs] = base + first[r];
+    }
   }
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    for (uint32_t m = w[j]; m; m &= m - 1u) {
-      if (pos < a.fcap) ids[pos] = (int32_t)((w0 + j) * 32 + (__ffs(m) - 1));
-      ++pos;
-    }
+  for (int r = 0; r < kRounds; ++r) {
+    int64_t pos = base + first[r];
+    const int32_t id0 = (w0 + r * kWave) * 32;
+    for (uint32_t m = w[r]; m; m &= m - 1u, ++pos)
+      if (pos < a.fcap) ids[pos] = id0 + (__ffs(m) - 1);
   }
 }
 
