@@ -638,8 +638,13 @@ __global__ void __launch_bounds__(kSageBlock, NT <= 3 ? 2 : 3) k_sage_layer(Laye
         for (int t = 0; t < Sp::CT; ++t) {
           const int cl = (ct0 + t) * 16 + il;
           if (cl >= a.ncols) continue;
-          float y = tot[r][t][e] + (a.bias && cl < a.d_out ? a.bias[cl] : 0.f);
-          if (a.relu && y < 0.f) y = 0.f;
+          // Columns past d_out hold zeros whatever the row holds: an infinity
+          // times their zero weights would be a NaN for the next layer.
+          float y = 0.f;
+          if (cl < a.d_out) {
+            y = tot[r][t][e] + (a.bias ? a.bias[cl] : 0.f);
+            if (a.relu && y < 0.f) y = 0.f;
+          }
           a.out[row * a.ncols + cl] = y;
         }
       }
@@ -762,9 +767,11 @@ __global__ void __launch_bounds__(kSageBlock) k_sage_mean(LayerArgs a, const flo
     for (int t = 0; t < KMAX; ++t)
       if (p[t] >= 0) sum += v[t];
     if (pv < 0 || sl >= a.ncols) continue;
-    float y = self + sum * (cnt ? 1.0f / (float)cnt : 0.f) +
-              (a.bias && sl < a.d_out ? a.bias[sl] : 0.f);
-    if (a.relu && y < 0.f) y = 0.f;
+    float y = 0.f;                     // zeros past d_out, as in k_sage_layer
+    if (sl < a.d_out) {
+      y = self + sum * (cnt ? 1.0f / (float)cnt : 0.f) + (a.bias ? a.bias[sl] : 0.f);
+      if (a.relu && y < 0.f) y = 0.f;
+    }
     a.out[r * a.ncols + sl] = y;
   }
 }
