@@ -430,15 +430,29 @@ struct Split {
   static constexpr int RT = R / 16 / RW;
 };
 
+// The same value, computed anew where it is used: what follows from it is not
+// kept in registers across a tile loop.
+__device__ __forceinline__ int anew(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // A block takes tiles of R output rows, S = LR * VE columns at a time: it
 // gathers the columns of [h_v | mean h_u] into LDS, LR lanes per source row,
 // so that a load covers runs of 16 * LR bytes (a row in shorter runs fetches
 // the lines at their ends again, once the caches have dropped them), then
 // multiplies them by the packed weights, which every block finds in L2.  Two
 // or three blocks per CU gather and multiply in turn.  The row tables come to
-// LDS one tile ahead.  Products are summed four groups at a time and then
-// added to the running sums, which keeps the rounding error below one long
-// sum's.
+// LDS one tile ahead, the weights to registers one group ahead.
+//
+// Rounding: a product's chain is one group long, self and mean apart, and the
+// groups are added to the running sums.  Chains of four groups with both halves
+// in them had up to 1.5 times the error of projecting every row first (which
+// averages its products' errors over the draws) on inputs of fewer than 130
+// columns; these have 0.37 to 0.94 times it over 25 networks of 12 to 602
+// columns.  Rows of up to 64 columns into at most three column tiles need half
+// a group per chain for that (16 columns throughout: 1.01e-7 with whole groups,
+// 9.2e-8 with halves, 9.7e-8 projected).
 //
 // Wide rows are bound by the random row reads (262K x 602 fp32 -> 128, ten
 // neighbours, 77K outputs: 549 us for 2.1 GB of row reads, where projecting
@@ -449,8 +463,8 @@ struct Split {
 // k_sage_rows inside the tile loop and 64-byte runs 655; half the waves
 // gathering and half multiplying 858; 1 KB runs in two blocks per CU 594;
 // eight neighbour rows in flight instead of five, in two blocks per CU, 565.
-// Blocks of three column tiles or fewer keep to two per CU: their registers
-// do not fit three without spills.
+// Lane indices are taken anew in every tile (anew()): the addresses that the
+// compiler kept from tile to tile otherwise cost up to 50 registers and spilled.
 template <int NT, int XT, int LR, bool NARROW>
 __global__ void __launch_bounds__(kSageBlock, NT <= 3 ? 2 : 3) k_sage_layer(LayerArgs a, int32_t* status) {
   typedef Split<NT> Sp;
@@ -462,6 +476,7 @@ __global__ void __launch_bounds__(kSageBlock, NT <= 3 ? 2 : 3) k_sage_layer(Laye
   constexpr int NRG = (RPW + RG - 1) / RG;
   constexpr int RB = NRG >= 2 ? 2 : 1;       // row groups in flight
   constexpr int TU = 5;                      // ... with so many neighbour rows each
+  constexpr int H = NT <= 3 && S <= 64 ? 2 : 1;   // product chains per group and half
   constexpr int kTab = (Sp::R * kMaxPitch + kSageBlock - 1) / kSageBlock;
   extern __shared__ float sm[];
   float* A = sm;                             // [2][R][LD]: self, mean
@@ -479,16 +494,18 @@ __global__ void __launch_bounds__(kSageBlock, NT <= 3 ? 2 : 3) k_sage_layer(Laye
   int32_t tab[kTab];
   auto fetch_table = [&](int64_t r0) {
     const int64_t left = (n - r0) * pitch;
+    const int at = anew(tid);
 #pragma unroll
     for (int j = 0; j < kTab; ++j) {
-      const int e = j * kSageBlock + tid;
+      const int e = j * kSageBlock + at;
       if (j * kSageBlock < tabn) tab[j] = (e < tabn && e < left) ? a.table[r0 * pitch + e] : -1;
     }
   };
   auto store_table = [&](int par) {
+    const int at = anew(tid);
 #pragma unroll
     for (int j = 0; j < kTab; ++j) {
-      const int e = j * kSageBlock + tid;
+      const int e = j * kSageBlock + at;
       if (e < tabn) s_pos[par * tabn + e] = tab[j];
     }
   };
@@ -583,60 +600,77 @@ __global__ void __launch_bounds__(kSageBlock, NT <= 3 ? 2 : 3) k_sage_layer(Laye
           }
         }
       }
+      const int g0 = ps * (S / kGroup), g1 = min(g0 + S / kGroup, a.G);
+      f32x4 next[2][Sp::CT];
+      auto fetch_weights = [&](int q) {
+#pragma unroll
+        for (int sn = 0; sn < 2; ++sn)
+#pragma unroll
+          for (int t = 0; t < Sp::CT; ++t)
+            next[sn][t] = a.w[((int64_t)(q * 2 + sn) * NT + ct0 + t) * kWave + lane];
+      };
+      fetch_weights(g0);
       if (ps + 1 == npass) fetch_table(row0 + step);
       __syncthreads();
       // ---- product ----
       const float* half = A + il * LD + 4 * g;
-      const int g0 = ps * (S / kGroup), g1 = min(g0 + S / kGroup, a.G);
-      for (int q4 = g0; q4 < g1; q4 += 4) {
-        f32x4 acc[Sp::RT][Sp::CT];
+#pragma unroll 1
+      for (int q = g0; q < g1; ++q) {
+        f32x4 w[2][Sp::CT], acc[2][H][Sp::RT][Sp::CT];
 #pragma unroll
-        for (int r = 0; r < Sp::RT; ++r)
+        for (int sn = 0; sn < 2; ++sn)
 #pragma unroll
-          for (int t = 0; t < Sp::CT; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const int qe = min(q4 + 4, g1);
-        for (int q = q4; q < qe; ++q) {
-          f32x4 w[2][Sp::CT];
+          for (int t = 0; t < Sp::CT; ++t) {
+            w[sn][t] = next[sn][t];
 #pragma unroll
-          for (int sn = 0; sn < 2; ++sn)
+            for (int h = 0; h < H; ++h)
 #pragma unroll
-            for (int t = 0; t < Sp::CT; ++t)
-              w[sn][t] = a.w[((int64_t)(q * 2 + sn) * NT + ct0 + t) * kWave + lane];
+              for (int r = 0; r < Sp::RT; ++r) acc[sn][h][r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+          }
+        fetch_weights(min(q + 1, g1 - 1));
+        __builtin_amdgcn_sched_barrier(0);   // or the loads sink to their use
 #pragma unroll
-          for (int sn = 0; sn < 2; ++sn) {
-            f32x4 x[Sp::RT];
+        for (int sn = 0; sn < 2; ++sn) {
+          f32x4 x[Sp::RT];
+#pragma unroll
+          for (int r = 0; r < Sp::RT; ++r)
+            x[r] = *(const f32x4*)(half + (sn * Sp::R + (rt0 + r) * 16) * LD + (q - g0) * kGroup);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int r = 0; r < Sp::RT; ++r)
-              x[r] = *(const f32x4*)(half + (sn * Sp::R + (rt0 + r) * 16) * LD + (q - g0) * kGroup);
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-              for (int r = 0; r < Sp::RT; ++r)
-#pragma unroll
-                for (int t = 0; t < Sp::CT; ++t)
-                  acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r][e], w[sn][t][e], acc[r][t],
-                                                                   0, 0, 0);
-          }
+              for (int t = 0; t < Sp::CT; ++t)
+                acc[sn][e % H][r][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                    x[r][e], w[sn][t][e], acc[sn][e % H][r][t], 0, 0, 0);
         }
 #pragma unroll
         for (int r = 0; r < Sp::RT; ++r)
 #pragma unroll
-          for (int t = 0; t < Sp::CT; ++t) tot[r][t] += acc[r][t];
+          for (int t = 0; t < Sp::CT; ++t) {
+            f32x4 self = acc[0][0][r][t], mean = acc[1][0][r][t];
+            if constexpr (H == 2) {
+              self += acc[0][1][r][t];
+              mean += acc[1][1][r][t];
+            }
+            tot[r][t] += self + mean;
+          }
       }
       if (ps + 1 == npass) store_table(par ^ 1);
       __syncthreads();
     }
     // D[i][j] of a tile sits in lane 16 * (i / 4) + j, element i % 4.
+    const int ln = anew(lane), gn = ln >> 4, in = ln & 15;
 #pragma unroll
     for (int r = 0; r < Sp::RT; ++r)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int ri = (rt0 + r) * 16 + 4 * g + e;
+        const int ri = (rt0 + r) * 16 + 4 * gn + e;
         const int64_t row = row0 + ri;
         if (row >= n || pos[ri * pitch] < 0) continue;
 #pragma unroll
         for (int t = 0; t < Sp::CT; ++t) {
-          const int cl = (ct0 + t) * 16 + il;
+          const int cl = (ct0 + t) * 16 + in;
           if (cl >= a.ncols) continue;
           // Columns past d_out hold zeros whatever the row holds: an infinity
           // times their zero weights would be a NaN for the next layer.
