@@ -519,6 +519,15 @@ __global__ void __launch_bounds__(kSageBlock, NT <= 3 ? 2 : 3) k_sage_layer(Laye
   int par = 0;
   for (; row0 < n; row0 += step, par ^= 1) {
     const int32_t* pos = s_pos + par * tabn;
+    // 1 / drawn neighbours of row lane % RPW of the wave, 0 for none: neighbour
+    // rows are scaled as they are added, so that the mean of finite rows is
+    // finite.
+    int drawn = 0;
+    for (int t = lane / RPW; t < a.k; t += kWave / RPW)
+      drawn += pos[(wv * RPW + lane % RPW) * pitch + 1 + t] >= 0;
+#pragma unroll
+    for (int o = RPW; o < kWave; o <<= 1) drawn += __shfl_xor(drawn, o, kWave);
+    const float share = drawn ? 1.0f / (float)drawn : 0.f;
     f32x4 tot[Sp::RT][Sp::CT];
 #pragma unroll
     for (int r = 0; r < Sp::RT; ++r)
@@ -549,11 +558,12 @@ __global__ void __launch_bounds__(kSageBlock, NT <= 3 ? 2 : 3) k_sage_layer(Laye
         const int tmax = __builtin_amdgcn_readfirstlane(m);
         u32x4 own[RB], v[RB * TU];
         Cols<XT> sum[RB];
-        int cnt[RB];
+        float inv[RB];
 #pragma unroll
         for (int i = 0; i < RB; ++i) {
           own[i] = load(rp[i][0]);
-          cnt[i] = 0;
+          const int r = (q + i) * RG + lr;
+          inv[i] = __shfl(share, r < RPW ? r : RPW - 1, kWave);
 #pragma unroll
           for (int e = 0; e < VE; ++e) sum[i].v[e] = 0.f;
         }
@@ -569,21 +579,17 @@ __global__ void __launch_bounds__(kSageBlock, NT <= 3 ? 2 : 3) k_sage_layer(Laye
 #pragma unroll
               for (int i = 0; i < RB; ++i) {
                 const bool ok = rp[i][1 + t0 + j] >= 0;
-                cnt[i] += ok;
 #pragma unroll
                 for (int e = 0; e < VE; ++e)
-                  sum[i].v[e] += ok ? element<XT>(v[i * TU + j], e) : 0.f;
+                  sum[i].v[e] = __builtin_fmaf(ok ? element<XT>(v[i * TU + j], e) : 0.f, inv[i],
+                                               sum[i].v[e]);
               }
         }
 #pragma unroll
         for (int i = 0; i < RB; ++i) {
-          const float inv = cnt[i] ? 1.0f / (float)cnt[i] : 0.f;
           Cols<XT> self;
 #pragma unroll
-          for (int e = 0; e < VE; ++e) {
-            self.v[e] = element<XT>(own[i], e);
-            sum[i].v[e] *= inv;
-          }
+          for (int e = 0; e < VE; ++e) self.v[e] = element<XT>(own[i], e);
           if (!NARROW) {
             shift_cols<XT>(self, past);
             shift_cols<XT>(sum[i], past);

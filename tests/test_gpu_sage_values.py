@@ -1,5 +1,5 @@
 """Values that the GraphSAGE layers must not lose on the way: infinities and
-NaNs, and digits.  Against the fp64 oracle."""
+NaNs, digits, and the largest finite features.  Against the fp64 oracle."""
 import numpy as np
 import pytest
 import torch
@@ -145,3 +145,21 @@ def test_no_more_rounding_error_than_projecting_first(fp16, dims, fanout):
                   for v in (got, projected_first(r, fanout, x, layers)))
     print(f"{err:.3e}, projected first {plain:.3e}: {err / plain:.3f}", flush=True)
     assert err <= 1.05 * plain
+
+
+@pytest.mark.parametrize("dims,fanout", [([12, 12, 5], (10, 5)), ([70, 64], (32,)),
+                                         ([300, 12, 20], (11, 10))])
+def test_means_of_huge_rows_are_finite(dims, fanout):
+    """Features of one sign close to the largest float: two of them overflow,
+    their mean does not."""
+    print(f"GraphSAGE {dims}, huge features, fan-out {fanout}", flush=True)
+    w, r, n = sampled(fanout)
+    rng = np.random.default_rng(dims[0])
+    x = (3.4e38 * rng.uniform(0.6, 1.0, (n, dims[0]))).astype(np.float32)
+    layers = _sage_layers(rng, dims)
+    layers[0] = (layers[0][0] * np.float32(2 ** -16), layers[0][1] * np.float32(2 ** -16),
+                 *layers[0][2:])
+    ref, ab = oracle_forward(r, fanout, x, layers)
+    got = forward(w, x, layers)[:ref.shape[0]].astype(np.float64)
+    assert np.isfinite(got).all()
+    assert np.all(np.abs(got - ref) <= _sage_tolerance(layers, list(fanout), ab))
