@@ -364,7 +364,7 @@ int gather_impl(const int32_t* in_ids_d, const int64_t* bounds_d, int32_t nseg, 
   const bool shared = (flags & GG_GATHER_SHARED) != 0;
   a.tile = copy_tile(tune, kf.row_bytes, 8192, !shared);
   a.pad_ = 0;
-  a.geom = copy_geom(kf.row_bytes, v16 ? 16 : 4);
+  a.geom = copy_geom(kf.row_bytes);
   const int32_t bx = blocks_per_seg(n_cap, nseg, tune, shared);
   const char* cache = (const char*)cache_d;
   char* out = (char*)out_d;

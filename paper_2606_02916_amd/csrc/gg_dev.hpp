@@ -179,7 +179,7 @@ __device__ __forceinline__ void sum_columns(const int32_t* p, int n, int cols, i
 // spread over the wave, so consecutive lanes move consecutive pieces of one
 // row and then of the next: every load and store instruction covers a
 // contiguous run of up to 1 KB, and short rows do not leave lanes idle.
-// Piece c belongs to row c / pieces, computed by chunk_row (copy_geom.hpp).
+// Piece c belongs to row c / pieces (piece_at, copy_geom.hpp).
 // VB is 16 for rows of 16 bytes and more, at whatever multiple of 4 the rows
 // start (global_load/store_dwordx4 need dword alignment only), and 4 for
 // narrower rows.  Bound by memory.  Moving unaligned rows in words held four
@@ -222,15 +222,6 @@ __device__ __forceinline__ void st_piece(char* p, typename Piece<VB>::val v) {
     __builtin_nontemporal_store(v, (GG_GLOBAL mem*)p);
   else
     *(GG_GLOBAL mem*)p = v;
-}
-
-// Row and byte of piece c.
-__device__ __forceinline__ uint32_t piece_at(const CopyGeom& g, uint32_t c, int vb,
-                                             uint32_t* row) {
-  const uint32_t r = chunk_row(c, g.pmagic);
-  const uint32_t off = (c - r * g.pieces) * (uint32_t)vb;
-  *row = r;
-  return off < g.last ? off : g.last;
 }
 
 template <int VB, bool NT, int U = (VB == 16 ? 4 : 8)>

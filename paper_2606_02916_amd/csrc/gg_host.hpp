@@ -102,11 +102,6 @@ int resolve_tuning(const gg_tuning_t* t, Tune* out);
 // step).
 int32_t copy_tile(const Tune& tune, int32_t row_bytes, int32_t max_bytes, bool pow2 = true);
 
-// Rows of 16 bytes and more move in 16-byte pieces whatever their alignment
-// (every base and stride is a multiple of 4, which is all the hardware's
-// 16-byte accesses need); narrower rows in words.
-inline bool copy_by_16(int32_t row_bytes) { return row_bytes >= 16; }
-
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 // Number of shards with rows whose memory is pinned host memory (read by

@@ -649,7 +649,7 @@ extern "C" int gg_stage_bulk(const int32_t* bucket_ids_d, const int64_t* owner_o
   a.cache_stride = cache_stride;
   a.tile = copy_tile(tune, kf.row_bytes, 32768);
   a.pad_ = 0;
-  a.geom = copy_geom(kf.row_bytes, v16 ? 16 : 4);
+  a.geom = copy_geom(kf.row_bytes);
 
   const int gridd = stage_delta_blocks(cap);
   GG_REQUIRE(ws && ws_bytes >= gg_ws_stage(cap, kp.P), "workspace of %zu bytes < %zu", ws_bytes,
@@ -739,7 +739,7 @@ extern "C" int gg_stage_inplace(const int32_t* bucket_ids_d, const int64_t* owne
   a.cache_stride = cache_stride;
   a.tile = copy_tile(tune, kf.row_bytes, 32768);
   a.pad_ = 0;
-  a.geom = copy_geom(kf.row_bytes, v16 ? 16 : 4);
+  a.geom = copy_geom(kf.row_bytes);
   GG_REQUIRE(((uintptr_t)occ_d & 15u) == 0 && ((uintptr_t)occ_prev_d & 15u) == 0,
              "occupancy maps must be 16-byte aligned");
   const int gridp = inplace_prep_blocks(cap, cache_rows);

@@ -1,8 +1,9 @@
-"""The row copy engine's chunk-to-row map, checked on the host for every
-row width the library accepts (no GPU needed): each 16- or 4-byte chunk
-of a 64-row tile must decode to its own row and column, including widths
-with one chunk per row or one tail word, whose divisor of 1 has no 32-bit
-multiplier."""
+"""The row copy engine's map from pieces to rows and bytes, checked on the host
+for every row width the library accepts (no GPU needed), with the code the
+kernels run: each 16- or 4-byte piece of a 64-row tile must decode to its own
+row, and a row's pieces (the last one overlapping the piece before it) must
+cover it, including widths of one piece per row, whose divisor of 1 has no
+32-bit multiplier."""
 import os
 import subprocess
 
