@@ -168,7 +168,8 @@ typedef struct gg_tuning {
                                 default: as many as fit in 32 KB (staging) or 8 KB (gathers),
                                 a power of two except for a GG_GATHER_SHARED gather */
   int32_t gather_blocks;     /* blocks of one gather launch, shared by its segments,
-                                8..65536 (default 1024, or 512 with GG_GATHER_SHARED) */
+                                8..65536 (default 1024, or 512 with GG_GATHER_SHARED, of
+                                which 64 to 256 work on windows of less than 340 MiB) */
   int32_t gather_loads;      /* 16-byte row loads in flight per lane in a gather: 2, 4 or 8
                                 (default 8) */
   int32_t stage_blocks;      /* most blocks of a staging copy, 1..65536 (default 16384) */
@@ -399,7 +400,7 @@ int gg_stage_inplace(const int32_t* bucket_ids_d, const int64_t* owner_off_d, in
  * No host synchronisation is needed.  Rows past n_cap are dropped and set
  * GG_DEV_CAPACITY.  flags: 0, or GG_GATHER_SHARED when other streams run
  * latency-bound work (sampling) on the device at the same time: the gather
- * then runs in half as many blocks, which costs it a few percent alone and
+ * then runs in half as many blocks or fewer, which slows it alone and
  * leaves room on the chip and in the memory system's queues for the
  * concurrent work, and a wavefront's tile of rows holds as many rows as fit
  * in 8 KB rather than a power of two.  Results are identical either way;

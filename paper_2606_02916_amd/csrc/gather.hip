@@ -1,7 +1,7 @@
 // gg_gather_batch: feature assembly of one or more consecutive batches
 // through the ID-to-slot remap, with the on-demand miss path.
 //
-// Grid (bx, nseg): blocks (., s) serve segment (batch) s, so every block's
+// Grid (bx, nseg), bx blocks to a segment (batch), so that every block's
 // statistics belong to one batch and reduce without atomics.  Each
 // wavefront takes a tile of consecutive output rows at a time (up to 64
 // rows and 8 KB); every lane of the tile resolves its row (local shard,
@@ -34,7 +34,23 @@ constexpr int kTilesPerBlock = kBlock / kWave;  // 4 waves
 // in flight with half the blocks, and the rest of the chip goes to the other
 // chain (six look-ahead windows of 1.5M 400-byte rows / 295K 2,408-byte rows:
 // 2,135 / 2,018 us, against 2,300 / 2,205 with 1,024, 2,205 / 2,117 with 768,
-// 2,204 / 2,018 with 448 and 2,221 / 1,987 with 512 and four loads).
+// 2,204 / 2,018 with 448 and 2,221 / 1,987 with 512 and four loads).  That is
+// for windows that the gather bounds.  In smaller ones the build is the longer
+// chain, and its small launches run slower on every CU that holds gather
+// blocks, whatever these keep in flight (one batch of 4,096 seeds, 79 MB of
+// rows, windows queued: 149 us with 512 blocks of eight loads or of two, 139
+// with 128 of eight).  So below kSharedWhole bytes only one block per
+// kSharedBytes works, 64 to 256 in all: the first of the grid, which the host
+// sizes before it knows the rows, so that they lie on as many CUs as they can.
+// Queued windows, 512 blocks / by bytes: 38 MB of rows 114 / 106 us, 79 MB 148 /
+// 138, 152 MB 180 / 169, 154 MB 183 / 169, 292 MB 230 / 214, 313 MB 265 / 245,
+// 351 MB of wide rows 222 / 200; six windows from start to end, 152 MB 1,210 /
+// 1,180, 292 MB 1,547 / 1,450.  Fewer blocks still (one per 786,432 bytes) cost
+// six windows of 154 MB 3%; from 370 MB on 256 blocks are no faster, and from
+// 450 MB slower (264 / 278).
+constexpr int64_t kSharedBytes = 5 << 17;
+constexpr int64_t kSharedWhole = 340LL << 20;
+constexpr int kSharedLeast = 64, kSharedMost = 256;
 
 struct GatherArgs {
   int64_t n_cap;        // output rows available
@@ -44,7 +60,7 @@ struct GatherArgs {
   int32_t nseg;
   int32_t nstat;        // 2 + P counters per block
   int32_t tile;         // rows per wave step (copy_tile)
-  int32_t pad_;
+  int32_t by_bytes;     // row bytes if the working blocks depend on them, else 0
   CopyGeom geom;
 };
 
@@ -57,6 +73,19 @@ __device__ __forceinline__ void seg_range(const int64_t* bounds, int s, const Ga
   h = h < l ? l : (h > a.n_cap ? a.n_cap : h);
   *lo = l;
   *hi = h;
+}
+
+// Blocks of a segment that work, of the grid's bx.
+__device__ __forceinline__ int working_blocks(const int64_t* bounds, const GatherArgs& a, int bx) {
+  if (!a.by_bytes) return bx;
+  int64_t rows = bounds[a.nseg] - bounds[0];
+  rows = rows < a.n_cap ? rows : a.n_cap;
+  const int64_t bytes = rows * a.by_bytes;
+  if (bytes >= kSharedWhole) return bx;
+  int blocks = (int)(bytes / kSharedBytes);
+  blocks = blocks < kSharedLeast ? kSharedLeast : (blocks > kSharedMost ? kSharedMost : blocks);
+  const int each = (blocks + a.nseg - 1) / a.nseg;
+  return each < bx ? each : bx;
 }
 
 // Row ids and owners of one tile, loaded ahead of its copy.
@@ -78,18 +107,21 @@ __global__ void __launch_bounds__(kBlock) k_gather_rows(const int32_t* in_ids, c
                                                         const char* cache, const int32_t* slot_of,
                                                         char* out, int32_t* blk_stat,
                                                         int32_t* status) {
+  const int bx = working_blocks(bounds, a, gridDim.x);
+  const int block = blockIdx.y * gridDim.x + blockIdx.x;
+  if (block >= bx * a.nseg) return;
+  const int seg = block / bx, x = block - seg * bx;
   __shared__ int64_t s_start[GG_MAX_PARTS + 1];
   __shared__ int32_t s_cnt[2 + GG_MAX_PARTS];  // local, hits, misses per owner
   for (int t = threadIdx.x; t <= GG_MAX_PARTS; t += blockDim.x) s_start[t] = part.start[t];
   for (int t = threadIdx.x; t < 2 + GG_MAX_PARTS; t += blockDim.x) s_cnt[t] = 0;
   __syncthreads();
-  const int seg = blockIdx.y;
   int64_t lo, hi;
   seg_range(bounds, seg, a, &lo, &hi);
   const int64_t begin = bounds[0];
   const int lane = lane_id();
   const int64_t ntiles = (hi - lo + a.tile - 1) / a.tile;
-  const int64_t step = (int64_t)gridDim.x * kTilesPerBlock;
+  const int64_t step = (int64_t)bx * kTilesPerBlock;
   int32_t st = 0;
   int32_t c_local = 0, c_hit = 0;
   // Software pipeline over the wave's tiles: while tile t is copied, the
@@ -106,7 +138,7 @@ __global__ void __launch_bounds__(kBlock) k_gather_rows(const int32_t* in_ids, c
       if (x.m != part.local) x.s = slot_of[x.u];
     }
   };
-  int64_t t = (int64_t)blockIdx.x * kTilesPerBlock + threadIdx.x / kWave;
+  int64_t t = (int64_t)x * kTilesPerBlock + threadIdx.x / kWave;
   TileIds cur = load_ids(t);
   load_slot(cur);
   TileIds nxt = load_ids(t + step);
@@ -163,7 +195,7 @@ __global__ void __launch_bounds__(kBlock) k_gather_rows(const int32_t* in_ids, c
   }
   if (st) set_status(status, st);
   __syncthreads();
-  int32_t* dst = blk_stat + ((int64_t)seg * gridDim.x + blockIdx.x) * a.nstat;
+  int32_t* dst = blk_stat + ((int64_t)seg * gridDim.x + x) * a.nstat;
   for (int t = threadIdx.x; t < a.nstat; t += blockDim.x) dst[t] = s_cnt[t];
 }
 
@@ -177,7 +209,7 @@ __global__ void __launch_bounds__(kBlock) k_gather_stats(const int64_t* bounds, 
   const int s = blockIdx.x;
   for (int t = threadIdx.x; t < 2 + GG_MAX_PARTS; t += blockDim.x) s_sum[t] = 0;
   __syncthreads();
-  sum_columns(blk_stat + (int64_t)s * bx * a.nstat, bx, a.nstat, s_sum);
+  sum_columns(blk_stat + (int64_t)s * bx * a.nstat, working_blocks(bounds, a, bx), a.nstat, s_sum);
   __syncthreads();
   gg_gather_stats_t* o = stats + s;
   if (threadIdx.x < GG_MAX_PARTS) {
@@ -363,7 +395,7 @@ int gather_impl(const int32_t* in_ids_d, const int64_t* bounds_d, int32_t nseg, 
   // than 20 and 3.
   const bool shared = (flags & GG_GATHER_SHARED) != 0;
   a.tile = copy_tile(tune, kf.row_bytes, 8192, !shared);
-  a.pad_ = 0;
+  a.by_bytes = shared && !tune.gather_blocks ? kf.row_bytes : 0;
   a.geom = copy_geom(kf.row_bytes);
   const int32_t bx = blocks_per_seg(n_cap, nseg, tune, shared);
   const char* cache = (const char*)cache_d;
