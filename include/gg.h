@@ -531,8 +531,8 @@ size_t gg_ws_sage(int64_t num_nodes, int32_t W, int64_t rows_cap, int32_t L,
  * window (layers_h[0].d_in elements of x_dtype per row at x_stride bytes;
  * at least min(rows_cap, |N_b| summed over the window) rows).  Rows are
  * found by rank in smp->frontier_bits, which must still hold the window's
- * N_b, as must the lists of every level (num_nodes is the graph's node
- * count).
+ * N_b, as must the offsets of every level and the lists of F_0 .. F_{L-1};
+ * N_b's own ids are not read (num_nodes is the graph's node count).
  * out_d receives the rows of F_0 (each batch's distinct seeds) of all
  * batches back to back, layers_h[L-1].d_out fp32 per row; out_rows_cap
  * bounds them.  The dense products run on MFMA in fp32 (a layer averages

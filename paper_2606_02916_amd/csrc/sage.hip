@@ -52,45 +52,24 @@ struct PackArgs {
   int32_t L;
 };
 
-// Blocks below nch * W: the rank prefixes of chunk c of batch b (rank[w / 4] =
-// set bits of the batch's set before word w).  The bits before the chunk are
-// the entries of the batch's ascending list N_b below the chunk's first id,
-// which the first wave finds in three or four rounds of 64 probes; summing the
-// chunks' bits would take a launch of its own and a second lookup per rank.
-// The other blocks pack the weights.
+// Blocks below nch * W: the rank prefixes within chunk c of batch b (rank[w / 4]
+// = set bits of the chunk before word w) and its bits (chunk[b * nch + c]).  The
+// other blocks pack the weights.
 __global__ void __launch_bounds__(kSageBlock) k_sage_prepare(const uint32_t* bits, int32_t nch,
-                                                             const int32_t* fids,
-                                                             const int64_t* nb_off, int32_t W,
-                                                             int2* rank, PackArgs pk,
-                                                             f32x4* packed) {
+                                                             int32_t W, int2* rank, int32_t* chunk,
+                                                             PackArgs pk, f32x4* packed) {
   __shared__ int32_t lds[kSageBlock / kWave];
-  __shared__ int64_t s_first;
   const int64_t nrank = (int64_t)nch * W;
   if ((int64_t)blockIdx.x < nrank) {
     const int64_t bc = blockIdx.x;   // b * nch + c: the chunks of all sets back to back
     const u32x4* p = (const u32x4*)(bits + bc * kRankChunk) + threadIdx.x * 2;
     const u32x4 x = p[0], y = p[1];
-    if (threadIdx.x < kWave) {
-      const int b = (int)(bc / nch);
-      const int32_t key = (int32_t)(bc - (int64_t)b * nch) * (kRankChunk * 32);
-      const int32_t* list = fids + nb_off[b];
-      int64_t lo = 0, hi = nb_off[b + 1] - nb_off[b];
-      while (lo < hi) {
-        const int64_t step = (hi - lo + kWave - 1) / kWave;
-        const int64_t at = lo + step * threadIdx.x;
-        const int below = (int)__popcll(__ballot(at < hi && list[at < hi ? at : lo] < key));
-        if (below == 0) break;
-        const int64_t first = lo + (int64_t)(below - 1) * step + 1;
-        hi = lo + (int64_t)below * step < hi ? lo + (int64_t)below * step : hi;
-        lo = first;
-      }
-      if (threadIdx.x == 0) s_first = lo;
-    }
     const int32_t sx = __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
     const int32_t sy = __popc(y.x) + __popc(y.y) + __popc(y.z) + __popc(y.w);
     int32_t tot;
-    const int32_t before = block_excl_scan<kSageBlock>(sx + sy, lds, &tot) + (int32_t)s_first;
+    const int32_t before = block_excl_scan<kSageBlock>(sx + sy, lds, &tot);
     rank[bc * kSageBlock + threadIdx.x] = make_int2(before, before + sx);
+    if (threadIdx.x == 0) chunk[bc] = tot;
     return;
   }
   const int64_t total = pk.first[pk.L];
@@ -111,6 +90,27 @@ __global__ void __launch_bounds__(kSageBlock) k_sage_prepare(const uint32_t* bit
   }
 }
 
+// Exclusive scan of each batch's chunk bits, one block per batch: for
+// more chunks than a wave scans at once.  Up to 64 (graphs of 4.2M nodes) the
+// blocks of the first kernel that looks ranks up scan them into LDS themselves
+// (chunk_starts), and one of them leaves the result for the next kernel: a launch
+// for it took 4 of the 36 us of a pass over 68K rows of 12 columns.
+constexpr int kChunkBlock = 1024;
+__global__ void __launch_bounds__(kChunkBlock) k_sage_chunks(const int32_t* chunk, int32_t* first,
+                                                             int32_t nch) {
+  __shared__ int32_t lds[kChunkBlock / kWave];
+  const int64_t at = (int64_t)blockIdx.x * nch;
+  int32_t carry = 0;
+  for (int32_t i0 = 0; i0 < nch; i0 += kChunkBlock) {
+    const int32_t i = i0 + threadIdx.x;
+    const int32_t v = i < nch ? chunk[at + i] : 0;
+    int32_t tot;
+    const int32_t before = block_excl_scan<kChunkBlock>(v, lds, &tot);
+    if (i < nch) first[at + i] = carry + before;
+    carry += tot;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Input rows of every output node.
 // ---------------------------------------------------------------------------
@@ -125,7 +125,10 @@ struct RowsArgs {
   const int32_t* nbr;
   const int64_t* noff;
   const uint32_t* bits;
-  const int32_t* rank;
+  const int32_t* rank;                 // set bits of the chunk before each 128-bit group
+  const int32_t* chunk;                // bits of each chunk
+  int32_t* before;                     // bits of the batch's set before each chunk
+  int32_t nch;
   int64_t wpb;
   int64_t rows_cap;
 };
@@ -138,7 +141,8 @@ struct Batch {
   int64_t nb0, nnb;        // N_b: first row, count
   int64_t slot0, nslot;    // the hop's neighbour slots: first (absolute), count
   const u32x4* bits;       // 128-bit groups of the batch's set
-  const int32_t* rank;     // set bits before each group
+  const int32_t* rank;     // set bits of the chunk before each group
+  int32_t chunk0;          // first chunk among all batches'
 };
 
 __device__ __forceinline__ Batch batch_at(const RowsArgs& a, int lvl, int b) {
@@ -155,6 +159,7 @@ __device__ __forceinline__ Batch batch_at(const RowsArgs& a, int lvl, int b) {
   t.nslot = a.noff[s + 1] - t.slot0;
   t.bits = (const u32x4*)(a.bits + (int64_t)b * a.wpb);
   t.rank = a.rank + (int64_t)b * (a.wpb / kRankWords);
+  t.chunk0 = b * a.nch;
   return t;
 }
 
@@ -184,11 +189,47 @@ __device__ __forceinline__ int64_t rank_in(u32x4 x, int32_t pre, int32_t u, int6
   return (mine & bit) && r < n ? r : -1;
 }
 
+// Set bits of the batch's set before its chunk c: in LDS (HERE) or in a.before.
+template <bool HERE>
+__device__ __forceinline__ int32_t chunk_first(const RowsArgs& a, const int32_t* s_chunk,
+                                               const Batch& t, uint32_t c) {
+  return HERE ? s_chunk[t.chunk0 + c] : a.before[t.chunk0 + c];
+}
+
+// The same for all chunks of all batches into LDS, a wave per batch (at most
+// kWave chunks each), and into a.before if asked to; the caller's next barrier
+// orders the stores.
+__device__ __forceinline__ void chunk_starts(const RowsArgs& a, int32_t* s_chunk, bool leave) {
+  constexpr int kWaves = kSageBlock / kWave, U = 4;
+  const int lane = lane_id();
+  for (int b0 = threadIdx.x / kWave; b0 < a.W; b0 += kWaves * U) {
+    int32_t v[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const int b = b0 + j * kWaves;
+      v[j] = b < a.W && lane < a.nch ? a.chunk[b * a.nch + lane] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const int b = b0 + j * kWaves;
+      const int32_t before = wave_incl_scan(v[j]) - v[j];
+      if (b < a.W && lane < a.nch) {
+        s_chunk[b * a.nch + lane] = before;
+        if (leave) a.before[b * a.nch + lane] = before;
+      }
+    }
+  }
+}
+
 // Position of u in the batch's N_b, or -1.
-__device__ __forceinline__ int64_t rank_of(const Batch& t, int64_t wpb, int32_t u) {
+template <bool HERE>
+__device__ __forceinline__ int64_t rank_of(const RowsArgs& a, const int32_t* s_chunk,
+                                           const Batch& t, int32_t u) {
   const uint32_t wi = (uint32_t)u >> 5;
-  if (u < 0 || wi >= (uint64_t)wpb) return -1;
-  return rank_in(t.bits[wi / kRankWords], t.rank[wi / kRankWords], u, t.nnb);
+  if (u < 0 || wi >= (uint64_t)a.wpb) return -1;
+  return rank_in(t.bits[wi / kRankWords],
+                 t.rank[wi / kRankWords] + chunk_first<HERE>(a, s_chunk, t, wi / kRankChunk), u,
+                 t.nnb);
 }
 
 __device__ __forceinline__ void level_offsets(const RowsArgs& a, int lvl, int64_t* off) {
@@ -198,15 +239,18 @@ __device__ __forceinline__ void level_offsets(const RowsArgs& a, int lvl, int64_
 }
 
 // Level blockIdx.y + 1 (1..L-1): each node's position, noted at its N_b row.
+template <bool HERE>
 __global__ void __launch_bounds__(kSageBlock) k_sage_places(RowsArgs a) {
+  extern __shared__ int32_t s_chunk[];
   __shared__ int64_t off[GG_MAX_W + 1];
   const int lvl = blockIdx.y + 1;
+  if (HERE) chunk_starts(a, s_chunk, blockIdx.x == 0 && blockIdx.y == 0);
   level_offsets(a, lvl, off);
   const int64_t n = off[a.W], f0 = a.off[(int64_t)lvl * a.W];
   for (int64_t r = (int64_t)blockIdx.x * kSageBlock + threadIdx.x; r < n;
        r += (int64_t)gridDim.x * kSageBlock) {
     const Batch t = batch_at(a, lvl, batch_of(off, r));
-    const int64_t p = rank_of(t, a.wpb, a.fids[f0 + r]);
+    const int64_t p = rank_of<HERE>(a, s_chunk, t, a.fids[f0 + r]);
     if (p >= 0 && t.nb0 + p < a.rows_cap) a.place[lvl][t.nb0 + p] = (int32_t)(r - t.out0);
   }
 }
@@ -217,8 +261,9 @@ __global__ void __launch_bounds__(kSageBlock) k_sage_places(RowsArgs a) {
 constexpr int kRowTile = 64;            // rows of a table tile
 constexpr int kRowJ = 3;                 // entries in flight per lane
 
-__device__ __forceinline__ void find_rows(const RowsArgs& a, int lvl, int64_t f0, int64_t f0in,
-                                          const Batch* bt, const int64_t (&r)[kRowJ],
+template <bool HERE>
+__device__ __forceinline__ void find_rows(const RowsArgs& a, const int32_t* s_chunk, int lvl,
+                                          int64_t f0, int64_t f0in, const Batch* bt, const int64_t (&r)[kRowJ],
                                           const int (&t)[kRowJ], const bool (&in)[kRowJ],
                                           int32_t (&row)[kRowJ], int32_t& st) {
   int32_t u[kRowJ], pre[kRowJ];
@@ -243,7 +288,7 @@ __device__ __forceinline__ void find_rows(const RowsArgs& a, int lvl, int64_t f0
     x[j] = u32x4{0u, 0u, 0u, 0u};
     if (ask[j]) {
       x[j] = bt->bits[wi / kRankWords];
-      pre[j] = bt->rank[wi / kRankWords];
+      pre[j] = bt->rank[wi / kRankWords] + chunk_first<HERE>(a, s_chunk, *bt, wi / kRankChunk);
     }
   }
   int64_t at[kRowJ];
@@ -278,8 +323,11 @@ __device__ __forceinline__ void find_rows(const RowsArgs& a, int lvl, int64_t f0
 // node (t = 0: itself, t = 1..k: its neighbour slots), or -1.  Bound by the
 // latency of its dependent random reads.  Nearly all tiles lie in one batch,
 // whose addresses are then the same for every lane.
+template <bool HERE>
 __global__ void __launch_bounds__(kSageBlock) k_sage_rows(RowsArgs a, int32_t* status) {
+  extern __shared__ int32_t s_chunk[];
   __shared__ int64_t off[GG_MAX_W + 1];
+  if (HERE) chunk_starts(a, s_chunk, false);
   const int lvl = a.L - 1 - (int)blockIdx.y;   // the largest level first
   level_offsets(a, lvl, off);
   const int64_t n = off[a.W] < a.rows_cap ? off[a.W] : a.rows_cap;
@@ -308,7 +356,7 @@ __global__ void __launch_bounds__(kSageBlock) k_sage_rows(RowsArgs a, int32_t* s
         t[j] = e - rr * (k + 1);
       }
       if (one) {
-        find_rows(a, lvl, f0, f0in, &bt, r, t, in, row, st);
+        find_rows<HERE>(a, s_chunk, lvl, f0, f0in, &bt, r, t, in, row, st);
       } else {
         // every lane goes through the batches its tile touches
         for (int bb = b; bb < a.W && off[bb] < row0 + rows; ++bb) {
@@ -318,7 +366,7 @@ __global__ void __launch_bounds__(kSageBlock) k_sage_rows(RowsArgs a, int32_t* s
 #pragma unroll
           for (int j = 0; j < kRowJ; ++j)
             mine[j] = in[j] && r[j] >= ob.out0 && r[j] < ob.out1;
-          find_rows(a, lvl, f0, f0in, &ob, r, t, mine, got, st);
+          find_rows<HERE>(a, s_chunk, lvl, f0, f0in, &ob, r, t, mine, got, st);
 #pragma unroll
           for (int j = 0; j < kRowJ; ++j) row[j] = mine[j] ? got[j] : row[j];
         }
@@ -854,6 +902,8 @@ struct SageWs {
   int32_t* table[GG_MAX_LAYERS];
   int32_t* place[GG_MAX_LAYERS];
   int32_t* rank;
+  int32_t* chunk;
+  int32_t* before;
   f32x4* packed;
 };
 
@@ -874,6 +924,8 @@ size_t sage_ws_layout(int64_t num_nodes, int32_t W, int64_t rows_cap, int32_t L,
   for (int32_t l = 0; l < L; ++l) w.table[l] = cv.take<int32_t>(r * kMaxPitch);
   for (int32_t l = 1; l < L; ++l) w.place[l] = cv.take<int32_t>(r);
   w.rank = cv.take<int32_t>((size_t)W * (size_t)(wpb / kRankWords));
+  w.chunk = cv.take<int32_t>((size_t)W * (size_t)(wpb / kRankChunk));
+  w.before = cv.take<int32_t>((size_t)W * (size_t)(wpb / kRankChunk));
   w.packed = cv.take<f32x4>((size_t)vecs);
   if (out) *out = w;
   return align_up(cv.used, 256);
@@ -1028,9 +1080,15 @@ extern "C" int gg_sage_forward(const gg_wsample_t* smp, int64_t num_nodes, int32
   }
   const int64_t pack_blocks = std::min<int64_t>(cdiv(pk.first[L], kSageBlock), 512);
   hipLaunchKernelGGL(k_sage_prepare, dim3((unsigned)(nch * W + pack_blocks)), dim3(kSageBlock), 0,
-                     stream, smp->frontier_bits, (int32_t)nch, smp->frontier_ids,
-                     smp->frontier_off + (int64_t)L * W, W, (int2*)sw.rank, pk, sw.packed);
+                     stream, smp->frontier_bits, (int32_t)nch, W, (int2*)sw.rank, sw.chunk, pk,
+                     sw.packed);
   GG_LAUNCH_CHECK("k_sage_prepare");
+  const bool here = nch <= kWave;
+  if (!here) {
+    hipLaunchKernelGGL(k_sage_chunks, dim3((unsigned)W), dim3(kChunkBlock), 0, stream, sw.chunk,
+                       sw.before, (int32_t)nch);
+    GG_LAUNCH_CHECK("k_sage_chunks");
+  }
   RowsArgs ra;
   ra.W = W;
   ra.L = L;
@@ -1046,17 +1104,24 @@ extern "C" int gg_sage_forward(const gg_wsample_t* smp, int64_t num_nodes, int32
   ra.noff = smp->nbr_off;
   ra.bits = smp->frontier_bits;
   ra.rank = sw.rank;
+  ra.chunk = sw.chunk;
+  ra.before = sw.before;
+  ra.nch = (int32_t)nch;
   ra.wpb = wpb;
   ra.rows_cap = rows_cap;
   const int64_t rows_grid =
       std::min<int64_t>(std::max<int64_t>(cdiv(rows_cap, kRowTile), 1), 1024);
+  const size_t chunk_lds = here ? (size_t)W * (size_t)nch * sizeof(int32_t) : 0;
   if (L > 1) {
-    hipLaunchKernelGGL(k_sage_places, dim3((unsigned)rows_grid, (unsigned)(L - 1)),
-                       dim3(kSageBlock), 0, stream, ra);
+    hipLaunchKernelGGL(here ? k_sage_places<true> : k_sage_places<false>,
+                       dim3((unsigned)rows_grid, (unsigned)(L - 1)), dim3(kSageBlock), chunk_lds,
+                       stream, ra);
     GG_LAUNCH_CHECK("k_sage_places");
   }
-  hipLaunchKernelGGL(k_sage_rows, dim3((unsigned)rows_grid, (unsigned)L), dim3(kSageBlock), 0,
-                     stream, ra, status_d);
+  const bool first = here && L == 1;
+  hipLaunchKernelGGL(first ? k_sage_rows<true> : k_sage_rows<false>,
+                     dim3((unsigned)rows_grid, (unsigned)L), dim3(kSageBlock),
+                     first ? chunk_lds : 0, stream, ra, status_d);
   GG_LAUNCH_CHECK("k_sage_rows");
 
   for (int32_t j = 0; j < L; ++j) {

@@ -163,3 +163,18 @@ def test_means_of_huge_rows_are_finite(dims, fanout):
     got = forward(w, x, layers)[:ref.shape[0]].astype(np.float64)
     assert np.isfinite(got).all()
     assert np.all(np.abs(got - ref) <= _sage_tolerance(layers, list(fanout), ab))
+
+
+def test_last_level_list_is_not_read():
+    """The rows of N_b are found by rank in the bit sets: the last level's id
+    list may have been overwritten since the gather."""
+    print("GraphSAGE without the last level's ids", flush=True)
+    dims, fanout = [20, 16, 7], (6, 5)
+    w, r, n = sampled(fanout)
+    rng = np.random.default_rng(4)
+    x = rng.standard_normal((n, dims[0])).astype(np.float32)
+    layers = _sage_layers(rng, dims)
+    ref, ab = oracle_forward(r, fanout, x, layers)
+    w.pipe.frontier_ids[int(r["foff"][len(fanout) * WK]):] = -5
+    got = forward(w, x, layers)[:ref.shape[0]].astype(np.float64)
+    assert np.all(np.abs(got - ref) <= _sage_tolerance(layers, list(fanout), ab))
