@@ -519,7 +519,8 @@ typedef struct gg_sage_layer {
 
 /* Workspace bytes of gg_sage_forward for graphs of num_nodes nodes, windows
  * of at most W batches and at most rows_cap rows per level (all batches
- * together; the frontier capacity of N_b bounds it). */
+ * together; the frontier capacity of N_b bounds it): mostly the hidden rows and,
+ * per level, GG_MAX_FANOUT + 1 row numbers for each row, whatever the fan-out. */
 size_t gg_ws_sage(int64_t num_nodes, int32_t W, int64_t rows_cap, int32_t L,
                   const gg_sage_layer_t* layers_h);
 

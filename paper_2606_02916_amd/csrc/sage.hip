@@ -909,18 +909,20 @@ struct SageWs {
 
 size_t sage_ws_layout(int64_t num_nodes, int32_t W, int64_t rows_cap, int32_t L,
                       const gg_sage_layer_t* layers, char* base, SageWs* out) {
-  int32_t dmax = 1;
+  // Layer j leaves its rows in h[j % 2]; the first layer's projected rows are
+  // done with when the second writes h[1], and share its place.
+  int32_t cols[2] = {0, layers[0].d_out <= kProjCols ? 32 : 0};
   int64_t vecs = 0;
   for (int32_t j = 0; j < L; ++j) {
-    if (j + 1 < L) dmax = std::max(dmax, inner_cols(layers[j].d_out));
+    if (j + 1 < L) cols[j & 1] = std::max(cols[j & 1], inner_cols(layers[j].d_out));
     vecs += packed_vecs(j ? inner_cols(layers[j - 1].d_out) : layers[j].d_in, layers[j].d_out);
   }
   const size_t r = (size_t)std::max<int64_t>(rows_cap, 1);
   const int64_t wpb = gg_bits_words(num_nodes);
   Carve cv{base, 0, ~(size_t)0};
   SageWs w;
-  for (int i = 0; i < 2; ++i) w.h[i] = cv.take<float>(r * (size_t)dmax);
-  w.z = cv.take<float>(layers[0].d_out <= kProjCols ? r * 32 : 0);
+  for (int i = 0; i < 2; ++i) w.h[i] = cv.take<float>(r * (size_t)cols[i]);
+  w.z = w.h[1];
   for (int32_t l = 0; l < L; ++l) w.table[l] = cv.take<int32_t>(r * kMaxPitch);
   for (int32_t l = 1; l < L; ++l) w.place[l] = cv.take<int32_t>(r);
   w.rank = cv.take<int32_t>((size_t)W * (size_t)(wpb / kRankWords));

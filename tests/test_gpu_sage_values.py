@@ -52,7 +52,8 @@ def forward(w, x, layers):
 
 @pytest.mark.parametrize("fp16,dims,fanout", [
     (False, [9, 12, 5], (4, 3)), (False, [300, 12, 20], (11, 10)),
-    (True, [70, 41, 20, 7], (5, 3, 2)), (True, [40, 100, 3], (4, 6))])
+    (True, [70, 41, 20, 7], (5, 3, 2)), (True, [40, 100, 3], (4, 6)),
+    (False, [300, 12, 100, 20, 9], (2, 3, 2, 10))])
 def test_infinities_and_nans_stay_where_the_formula_puts_them(fp16, dims, fanout):
     """Features of +inf, -inf and NaN, hidden widths between whole column tiles
     (the second case projects its first layer).  Hidden units see a +inf of the
