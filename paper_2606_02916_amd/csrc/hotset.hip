@@ -155,7 +155,7 @@ __global__ void __launch_bounds__(1024) k_hot_select(const int32_t* chunk_hist, 
   __syncthreads();
   // Threads in whole rows of W + 1 counts: each keeps to one frequency, eight
   // loads in flight (one pass per frequency waited for memory W times: 11.1 us
-  // at W = 16 over 608 chunks, now 4.4).
+  // at W = 16 over 304 chunks, now 4.4).
   const int cols = W + 1, rows = (int)blockDim.x / cols;
   if ((int)threadIdx.x < rows * cols) {
     const int f = threadIdx.x % cols;

@@ -2,26 +2,28 @@
 // sampled blocks of a window (Algorithm 1 forward pass; Sec. VI-A model), all
 // W batches of the window at once.
 //
-// Three launches prepare a call: the ranks in the N_b bit sets and the weights
-// in matrix-core order (k_sage_prepare), each node's place in its own level (k_sage_places), and
-// for every output node the input rows of itself and of its neighbours
-// (k_sage_rows, every level in one launch).  Random lookups run there, with
-// one thread each, and not in front of the row reads.  Then each layer,
+// Three launches prepare a call (four on graphs of more than 4.2M nodes): the
+// rank prefixes of the N_b bit sets and the weights in matrix-core order
+// (k_sage_prepare), each node's place in its own level (k_sage_places), and for
+// every output node the input rows of itself and of its neighbours (k_sage_rows,
+// every level in one launch).  Random lookups run there, with one thread each,
+// and not in front of the row reads.  Then each layer,
 // out_v = act(W_self^T h_v + W_neigh^T mean_{u in S(v)} h_u + bias), takes one
 // of two forms (use_projection says which):
-//  * k_sage_layer: a wave builds [h_v | mean h_u] of 16 output nodes in the
-//    registers that the fp32 MFMA reads (v_mfma_f32_16x16x4f32), a few column
-//    groups at a time, and multiplies them by the weights in LDS.  Nothing is
-//    projected that no output needs, and no projected row goes through memory;
+//  * k_sage_layer: a block gathers [h_v | mean h_u] of 32 or 64 output nodes
+//    into LDS, up to 128 columns at a time, and multiplies them on the fp32
+//    matrix cores (v_mfma_f32_16x16x4f32) by weights that come from L2 to
+//    registers.  Nothing is projected that no output needs, and no projected row
+//    goes through memory;
 //  * k_sage_project and k_sage_mean: Z = H [W_self | W_neigh] for every input
 //    row, then the mean of projected rows, which commutes with the linear
 //    map: where rows are wide and outputs narrow, each input row is read once
 //    and the random reads are of 128-byte rows.
 //
-// A node's row in level N_b is its rank in the batch's N_b bit set: a prefix
-// per 256 bits plus popcounts of the bits before the node.  In other levels it
-// is its position in the ascending frontier, which k_sage_places notes at the
-// node's N_b row.
+// A node's row in level N_b is its rank in the batch's N_b bit set: the set bits
+// before its chunk of 65,536 nodes, those of the chunk before its group of 128,
+// and popcounts of the bits before it there.  In other levels it is its position
+// in the ascending frontier, which k_sage_places notes at the node's N_b row.
 #include <hip/hip_fp16.h>
 
 #include "gg_host.hpp"
@@ -35,7 +37,7 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 constexpr int kSageBlock = 256;          // 4 waves
 constexpr int kTileRows = 64;            // 16 rows per wave
 constexpr int kGroup = 16;               // columns of the left operand per MFMA group
-constexpr int kWLdsBytes = 65536;        // weights in LDS at most (two blocks per CU)
+constexpr int kWLdsBytes = 65536;        // weights of k_sage_project in LDS at most
 constexpr int kRankWords = 4;            // bit-set words per rank prefix
 constexpr int kRankChunk = kSageBlock * 2 * kRankWords;   // words per rank chunk
 constexpr int kMaxPitch = GG_MAX_FANOUT + 1;
@@ -949,7 +951,8 @@ int launch_layer(LayerArgs& a, int64_t rows_bound, int32_t* status, hipStream_t 
 }
 
 // Lanes per source row: the row in one load of a few rows where it is narrow,
-// else the widest run whose operand tile leaves room for two blocks per CU.
+// else a run of 128 columns.  Its operand tile leaves LDS for three blocks per CU
+// with 32 output rows, and with 64 for two up to a fan-out of 27, for one above.
 template <int NT, int XT>
 int launch_layer_u(LayerArgs& a, int64_t rows_bound, int32_t* status, hipStream_t stream) {
   constexpr int VE = Cols<XT>::VE;

@@ -126,9 +126,9 @@ inline bool last_hop_slices(int64_t num_nodes, int32_t W, const Tune& tune) {
 // the counting and emitting passes read the flags and only the flagged blocks
 // (16 sets over 111M nodes, 222 MB: the two passes of levels 0, 1 and 2 take
 // 29, 35 and 58 us instead of about 190 each, those of the last, whose marks
-// touch 44% of the blocks, 118).  Taken where a window's sets are far larger than the caches and marks
-// are atomic ORs (too many LDS slices); smaller sets, whose passes are launch
-// latency, keep one block per chunk.  A tuning that turns off LDS slices and
+// touch 44% of the blocks, 118).  Taken where a window's sets are far larger than
+// the caches and marks are atomic ORs (too many LDS slices); smaller sets, whose
+// passes are launch latency, keep one block per chunk.  A tuning that turns off LDS slices and
 // the byte map takes it at any size.
 constexpr int64_t kFlagMinBytes = 32LL << 20;   // least bytes of a window's sets
 constexpr int kFlagWords = 16;                  // words per flag

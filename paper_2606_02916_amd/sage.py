@@ -1,7 +1,7 @@
 """The consumer of X_b: GraphSAGE with the mean aggregator over a window's
 sampled blocks (Algorithm 1's forward pass on the assembled tensor; the
 paper trains a GraphSAGE model, Sec. VI-A).  Buffers and argument
-marshalling only; both kernels per layer run in libgg."""
+marshalling only; the row lookups and the layers run in libgg."""
 from __future__ import annotations
 
 import torch

@@ -495,18 +495,25 @@ class LookaheadPipeline:
         # from 0.86 to 0.77 ms).  The sequential driver, alone on the chip,
         # keeps the library's defaults.  A caller's tuning replaces this one
         # as a whole.
+        # With shards in host memory the gather runs beside a staging whose
+        # waves wait for PCIe on half of the CUs; few blocks of many loads end
+        # with that staging and hold up the build after next (111M nodes, three
+        # shards in host memory: windows end in pairs, 0.9 and 6.0 ms apart,
+        # 3.48 ms each; with twice the blocks of four loads 3.25 apart, 3.43
+        # each).
+        on_host = any(t is not None and not t.is_cuda for t in shards)
         shared = last_hop_sharing(self.N, self.fanout, max_batch, self.W) >= 2.0
         if tuning is None:
             dense = last_hop_density(self.N, self.fanout, max_batch) >= 1.0
             tiles = self.L >= 3 or shared
             tuning = gg.make_tuning(
                 sample_order=gg.GG_SAMPLE_TILES_LAST if tiles else gg.GG_SAMPLE_BATCH_ORDER,
-                **({} if dense else {"bytemap_max_mb": LOOKAHEAD_BYTEMAP_MAX_MB}))
+                **({} if dense else {"bytemap_max_mb": LOOKAHEAD_BYTEMAP_MAX_MB}),
+                **({"gather_blocks": 1024, "gather_loads": 4} if on_host else {}))
         self.tuning = tuning
         self.geo = g = _Geometry(self.N, self.W, self.fanout, max_batch, self.P, local_owner,
                                  shard_rows, self.stride, self.cache_stride, tuning)
         dev = self.device
-        on_host = any(t is not None and not t.is_cuda for t in shards)
         if nsets is None:
             nsets = 2 if on_host else 3
         if int(nsets) < 2:

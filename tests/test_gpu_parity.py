@@ -148,7 +148,7 @@ def test_fanout_above_every_degree_is_the_bfs_ball():
 
 
 def test_unaligned_rows_use_the_word_path():
-    log("tiny: 44-byte rows at a 44-byte stride, 4-byte copy path")
+    log("tiny: 44-byte rows at a 44-byte stride (16-byte pieces at any multiple of 4)")
     inst = synth.instance("tiny")
     rng = np.random.default_rng(5)
     shards = [rng.integers(0, 256, size=(s.shape[0], 44), dtype=np.uint8) for s in inst.shards]
@@ -157,7 +157,7 @@ def test_unaligned_rows_use_the_word_path():
 
 
 def test_row_with_tail_words():
-    log("tiny: 1 KB + 12 byte rows at a 16-byte-aligned stride (vector path with tail)")
+    log("tiny: 1 KB + 12 byte rows at a 16-byte-aligned stride (an overlapping last piece)")
     inst = synth.instance("tiny")
     rng = np.random.default_rng(6)
     shards = [rng.integers(0, 256, size=(s.shape[0], 1040), dtype=np.uint8) for s in inst.shards]
@@ -168,13 +168,13 @@ def test_row_with_tail_words():
 @pytest.mark.parametrize("rows", [(4, 4), (4, 16), (16, 16), (20, 20), (20, 32), (100, 100),
                                   (100, 112), (1204, 1204), (1204, 1216)])
 def test_row_widths_with_one_chunk_or_one_tail_word(rows):
-    """Row widths whose copy geometry has a divisor of 1: one 16-byte chunk
-    per row (16 and 20 bytes), one 4-byte tail word (4, 20, 100 and 1,204
-    bytes on the vector path) or one word per row (4 bytes on the word
-    path), with strides that are and are not multiples of 16.  Through
-    k_stage_rows and both gathers with a budget that leaves misses
-    (k_gather_finish), then through in-place staging (k_inplace_rows) over
-    two windows with the union."""
+    """Row widths at the edges of the copy geometry: one word per row (4
+    bytes) and one 16-byte piece (16 bytes), whose divisor is 1, and rows
+    that end one word into a piece (20, 100 and 1,204 bytes: the last piece
+    overlaps the one before it), with strides that are and are not multiples
+    of 16.  Through k_stage_rows and both gathers with a budget that leaves
+    misses, then through in-place staging (k_inplace_rows) over two windows
+    with the union."""
     rb, stride = rows
     log(f"tiny: {rb}-byte rows at stride {stride}")
     inst = synth.instance("tiny")
