@@ -598,13 +598,25 @@ __device__ __forceinline__ int64_t level_place(int c, int b, int nch, const int3
 }
 
 // Writes the ids of one chunk of one batch's bit set, ascending, at its
-// place in the level's list.  A wave takes 512 consecutive words in eight
-// rounds of 64, one word per lane, so that the lanes' ids of a round lie side
-// by side in the list and their stores fall into a few lines (with eight
-// consecutive words per lane every store of a wave touched up to 64: beside a
-// gather, the dense lists of the 233K-node graph, 33K ids per batch, took 15.9
-// us a level, now 11.3).  The rounds' counts are
-// scanned two to a register.
+// place in the level's list, in one of two ways.  Sparse levels: a thread writes
+// those of its eight consecutive words, behind one scan.  Dense ones (ROUNDS): a
+// wave takes 512 consecutive words in eight rounds of 64, one word per lane, so
+// that the lanes' ids of a round lie side by side in the list and their stores
+// fall into a few lines (with eight consecutive words per lane every store of a
+// wave touches up to 64: beside a gather, the dense lists of the 233K-node graph,
+// 33K ids per batch, took 15.9 us a level, now 11.3); the rounds' counts are
+// scanned two to a register.  The host's bound on a batch's entries decides
+// (rounds from N / kRoundsShare on, and for the seeds, whose bound is their
+// count and not several times it, from N / kRoundsSeeds).  Levels of 16 batches of 1,024 on the
+// 2.45M-node graph, alone, rounds / consecutive words: bound at 0.04% of the
+// nodes 6.8 / 6.1 us, at 0.7% 6.5 / 5.7, at 7% 7.6 / 7.0, at 44% 9.2 / 12.1; four
+// of 256 on the 10K-node graph, at 2.6% (seeds) 5.7 / 6.3, at 28% 6.8 / 7.7, at
+// all 7.4 / 9.1.  On larger
+// graphs every level is sparse: sampling 16 batches of 1,024 on 20M nodes took
+// 271 us in rounds, and takes 250.
+constexpr int kRoundsShare = 8, kRoundsSeeds = 64;
+
+template <bool ROUNDS>
 __global__ void __launch_bounds__(kBlock) k_bits_emit(const uint32_t* bits, int64_t wpb,
                                                       const int32_t* cnt, Totals tt,
                                                       int32_t* ids, int64_t* frontier_off,
@@ -615,6 +627,28 @@ __global__ void __launch_bounds__(kBlock) k_bits_emit(const uint32_t* bits, int6
   static_assert(kWave * 32 < 1 << 16, "a round's counts fit in 16 bits");
   __shared__ int32_t s_wave[kBlock / kWave];
   const int c = blockIdx.x, b = blockIdx.y, nch = gridDim.x;
+  if constexpr (!ROUNDS) {
+    const int32_t w0 = c * kChunkWords + threadIdx.x * kWordsPerThread;
+    const u32x4* p = (const u32x4*)(bits + (int64_t)b * wpb + w0);
+    const u32x4 x = p[0], y = p[1];    // in flight while the offsets are summed
+    const int64_t off =
+        level_place(c, b, nch, cnt, tt, frontier_off, nbr_off, ls, need, status, a);
+    const uint32_t w[kWordsPerThread] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+    int32_t n = 0, tot;
+#pragma unroll
+    for (int j = 0; j < kWordsPerThread; ++j) n += __popc(w[j]);
+    int64_t pos = off + block_excl_scan<kBlock>(n, s_wave, &tot);
+    if (a.tile_runs) {
+      // this thread's run of 8 words starts a tile every tile_runs runs
+      const int64_t run = (int64_t)c * kBlock + threadIdx.x;
+      if (run % a.tile_runs == 0) a.tstart[(int64_t)b * a.ntiles + run / a.tile_runs] = pos;
+    }
+#pragma unroll
+    for (int j = 0; j < kWordsPerThread; ++j)
+      for (uint32_t m = w[j]; m; m &= m - 1u, ++pos)
+        if (pos < a.fcap) ids[pos] = (w0 + j) * 32 + (__ffs(m) - 1);
+    return;
+  }
   const int lane = lane_id(), wv = threadIdx.x / kWave;
   const int32_t w0 = c * kChunkWords + wv * (kRounds * kWave) + lane;   // the first round's word
   const uint32_t* p = bits + (int64_t)b * wpb + w0;
@@ -1265,9 +1299,10 @@ int sample_window_impl(const gg_csr_t* csr, const int32_t* seeds_d, const int64_
       GG_LAUNCH_CHECK("k_flag_emit");
       continue;
     }
-    hipLaunchKernelGGL(k_bits_emit, dim3(nch, W), dim3(kBlock), 0, stream, out->frontier_bits, wpb,
-                       sw.cnt, tt, out->frontier_ids, out->frontier_off, out->nbr_off, sw.lvl,
-                       out->need, status_d, la);
+    const bool rounds = bbound[lv] * (lv == 0 ? kRoundsSeeds : kRoundsShare) > N;
+    hipLaunchKernelGGL(rounds ? k_bits_emit<true> : k_bits_emit<false>, dim3(nch, W), dim3(kBlock),
+                       0, stream, out->frontier_bits, wpb, sw.cnt, tt, out->frontier_ids,
+                       out->frontier_off, out->nbr_off, sw.lvl, out->need, status_d, la);
     GG_LAUNCH_CHECK("k_bits_emit");
   }
   return GG_OK;
