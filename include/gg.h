@@ -196,8 +196,9 @@ typedef struct gg_tuning {
                                 64 KB: 524,288 node ids), when a batch's set has at most this many
                                 slices, 1..4096; -1: never (the hop marks with atomic ORs, or
                                 the last hop into the byte map).  Default 8.  Without slices,
-                                32 MB of sets and more (any size with bytemap_max_mb -1 too) also
-                                flag their marked blocks, and the compaction reads only those */
+                                48 MB of sets and more with at most 16 possible entries per 512
+                                nodes (any set with bytemap_max_mb -1 too) also flag their
+                                marked blocks, and the compaction reads only those */
   int32_t mark_slice_chunks; /* chunks of 65,536 node ids (8 KB of a set) per mark slice, 1..8
                                 (default 8) */
   int32_t mark_block;        /* lanes of a mark block: 256 (default) or 1024; a block keeps

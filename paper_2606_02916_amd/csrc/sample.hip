@@ -127,16 +127,28 @@ inline bool last_hop_slices(int64_t num_nodes, int32_t W, const Tune& tune) {
 // (16 sets over 111M nodes, 222 MB: the two passes of levels 0, 1 and 2 take
 // 29, 35 and 58 us instead of about 190 each, those of the last, whose marks
 // touch 44% of the blocks, 118).  Taken where a window's sets are far larger than
-// the caches and marks are atomic ORs (too many LDS slices); smaller sets, whose
-// passes are launch latency, keep one block per chunk.  A tuning that turns off LDS slices and
-// the byte map takes it at any size.
-constexpr int64_t kFlagMinBytes = 32LL << 20;   // least bytes of a window's sets
+// the caches and marks are atomic ORs (too many LDS slices), and where the last
+// level leaves blocks empty, which it does while the host's bound on a batch's
+// entries is at most 16 per block (batches overlap and reach far fewer).  Smaller
+// sets, whose passes are launch latency, and denser ones keep one block per
+// chunk.  Sampling a window, flags / none: 16 batches of 1,024, three hops, 20M
+// nodes (38 MB, 28 entries per block) 287 / 250 us, 33M (63 MB, 17) 299 / 300,
+// 40M (76 MB, 14) 304 / 317; of 4,096 on 40M (55) 658 / 608; 111M nodes (5), three
+// batches (40 MB) 167 / 163, four (53 MB) 177 / 191, six (79 MB) 204 / 255; two
+// hops of 16 batches on 33M (1) 110 / 139.  A tuning that turns off LDS slices and the byte map takes flags at any size.
+constexpr int64_t kFlagMinBytes = 48LL << 20;   // least bytes of a window's sets
+constexpr int kFlagEntries = 16;                // most entries bound per block of 512 nodes
 constexpr int kFlagWords = 16;                  // words per flag
 constexpr int kFlagChunks = 16;                 // chunks per emit block
 
+inline bool flags_forced(const Tune& tune) {
+  return tune.mark_slices_max < 0 && tune.bytemap_max_bytes < 0;
+}
+
+// Whether the workspace has room for flags: the choice but for the entries.
 inline bool use_flags(int64_t num_nodes, int32_t W, const Tune& tune) {
   if (use_slices(num_nodes, tune)) return false;
-  if (tune.mark_slices_max < 0 && tune.bytemap_max_bytes < 0) return true;
+  if (flags_forced(tune)) return true;
   return (int64_t)W * gg_bits_words(num_nodes) * 4 >= kFlagMinBytes;
 }
 
@@ -1145,6 +1157,17 @@ int sample_window_impl(const gg_csr_t* csr, const int32_t* seeds_d, const int64_
   int64_t max_batch = 0;
   for (int b = 0; b < W; ++b)
     max_batch = std::max<int64_t>(max_batch, seed_off_h[b + 1] - seed_off_h[b]);
+  // Host bound on the largest batch's entries, by level.
+  int64_t bbound[GG_MAX_LAYERS + 1];
+  {
+    int64_t lev = std::min<int64_t>(max_batch, N);
+    for (int l = 0; l <= L; ++l) {
+      bbound[l] = lev;
+      if (l < L) lev = std::min<int64_t>(lev * (fanout_h[l] + 1), N);
+    }
+  }
+  if (sw.flags && !flags_forced(tune) && bbound[L] > wpb / kFlagWords * kFlagEntries)
+    sw.flags = nullptr;
   // With few chunks in the window, level 0's counts come from k_seed_bits
   // and its emit sums them directly: one launch fewer.  Beside a running
   // gather even a small launch costs 7-12 us.
@@ -1189,14 +1212,6 @@ int sample_window_impl(const gg_csr_t* csr, const int32_t* seeds_d, const int64_
   // Hop lv - 1 (making level lv) marks through LDS slices when the graph's
   // sets split into few slices and, before the last hop, when its bound on
   // slots per batch reaches the tuning's minimum.
-  int64_t bbound[GG_MAX_LAYERS + 1];   // entries of the largest batch, by level
-  {
-    int64_t lev = std::min<int64_t>(max_batch, N);
-    for (int l = 0; l <= L; ++l) {
-      bbound[l] = lev;
-      if (l < L) lev = std::min<int64_t>(lev * (fanout_h[l] + 1), N);
-    }
-  }
   auto lds_marks = [&](int lv) {
     if (lv == L) return last_slices;
     return slices && W >= min_batches(false, tune) &&

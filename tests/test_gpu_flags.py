@@ -1,5 +1,5 @@
 """Block flags of the sampler's sets at the size where the library takes them by
-itself: 64 batches over 4.3M nodes, too many LDS slices and 34 MB of sets.  With
+itself: 64 batches over 6.4M nodes, too many LDS slices and 51 MB of sets.  With
 the byte map at the last hop (the library's choice there: its marks set no
 flags), and with atomics throughout.  Against the oracle."""
 import numpy as np
@@ -11,7 +11,7 @@ from tests.gpu_util import World
 
 pytestmark = pytest.mark.gpu
 
-N, W = 4_300_000, 64
+N, W = 6_400_000, 64
 
 
 @pytest.fixture(scope="module")
@@ -35,7 +35,8 @@ def test_flagged_sets_match_oracle(inst, fields):
     print(f"{W} batches over {N} nodes, tuning {fields}", flush=True)
     from paper_2606_02916_amd import gg
     words = gg.gg_bits_words(N)
-    assert W * words * 4 >= 32 << 20 and words > 8 * 8 * 2048      # flags, no LDS slices
+    assert W * words * 4 >= 48 << 20 and words > 8 * 8 * 2048      # flags, no LDS slices
+    assert 30 * 5 * 4 * 3 <= words // 16 * 16                      # few entries per block
     assert W * words * 32 <= 512 << 20                             # the byte map fits
     w = World(inst, W=W, tuning=gg.make_tuning(**fields))
     sizes = np.full(W, 30)
