@@ -762,9 +762,8 @@ struct ProjArgs {
 // Each wave owns 16 rows and loads them straight into registers, 16 bytes per
 // lane; bound by those reads and the 128 bytes written per row (1.56M rows of
 // 400 bytes in 190 us, 4.3 TB/s).
-template <int XT>
 __global__ void __launch_bounds__(kSageBlock, 8) k_sage_project(ProjArgs a) {
-  constexpr int VE = Cols<XT>::VE, ES = 16 / VE, MG = VE / 4;
+  constexpr int VE = Cols<GG_F32>::VE;                   // one group per load
   constexpr int UL = 4;                                  // loads in flight per lane
   constexpr int kGroupW = 2 * kWave;
   extern __shared__ f32x4 swl[];
@@ -782,36 +781,28 @@ __global__ void __launch_bounds__(kSageBlock, 8) k_sage_project(ProjArgs a) {
     const int64_t r = row0 + il < n ? row0 + il : n - 1;
     const char* rp = a.h + r * a.h_stride;
     f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-    for (int s = 0; s * MG < a.G; s += UL) {
+    for (int s = 0; s < a.G; s += UL) {
       u32x4 raw[UL];
 #pragma unroll
       for (int u = 0; u < UL; ++u) {
         const int c = (s + u) * 4 * VE + VE * g;
-        if ((s + u) * MG < a.G) raw[u] = load16(rp + (c < a.K - VE ? c : a.K - VE) * ES);
+        if (s + u < a.G) raw[u] = load16(rp + (c < a.K - VE ? c : a.K - VE) * 4);
       }
 #pragma unroll
       for (int u = 0; u < UL; ++u) {
-        if ((s + u) * MG >= a.G) break;
+        if (s + u >= a.G) break;
         const int past = (s + u) * 4 * VE + VE * g + VE - a.K;
-        Cols<XT> v;
+        Cols<GG_F32> v;
 #pragma unroll
-        for (int e = 0; e < VE; ++e) v.v[e] = element<XT>(raw[u], e);
-        if ((s + u + 1) * 4 * VE > a.K) shift_cols<XT>(v, past);
+        for (int e = 0; e < VE; ++e) v.v[e] = element<GG_F32>(raw[u], e);
+        if ((s + u + 1) * 4 * VE > a.K) shift_cols<GG_F32>(v, past);
 #pragma unroll
-        for (int m = 0; m < MG; ++m) {
-          // columns 4 VE (s + u) + VE g + 4 m .. + 3, where the packed
-          // weights have them
-          const int cg = (s + u) * VE + MG * g + m;      // in fours of columns
-          const bool in = cg / 4 < a.G;
+        for (int sn = 0; sn < 2; ++sn) {
+          // columns 16 (s + u) + 4 g .. + 3, where the packed weights have them
+          const f32x4 b = wl[((s + u) * 2 + sn) * kWave + g * 16 + il];
 #pragma unroll
-          for (int sn = 0; sn < 2; ++sn) {
-            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-            const f32x4 b = in ? wl[(cg / 4 * 2 + sn) * kWave + cg % 4 * 16 + il] : zero;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              acc[sn] = __builtin_amdgcn_mfma_f32_16x16x4f32(v.v[m * 4 + e], b[e], acc[sn], 0, 0,
-                                                             0);
-          }
+          for (int e = 0; e < 4; ++e)
+            acc[sn] = __builtin_amdgcn_mfma_f32_16x16x4f32(v.v[e], b[e], acc[sn], 0, 0, 0);
         }
       }
     }
@@ -880,18 +871,22 @@ int64_t packed_vecs(int32_t cols, int32_t d_out) {
   return cdiv(cols, kGroup) * 2 * col_tiles(d_out) * kWave;
 }
 
-// A layer projects every input row first when reading the k + 1 input rows of
-// each output node would move more than twice as much: an input row read once
-// and 128 bytes written, and k + 1 lines of 128 bytes, against k + 1 rows with
-// about a line each for their unaligned ends.  A level holds about half as
-// many rows per output node as its hop draws, at most about four on dense
-// graphs.  The factor is for the rows that the caches serve again when they
-// are gathered.  Whole forward passes, projected / gathered first layers: 602
-// fp32 -> 16, ten neighbours, 286 / 385 us; 300 fp32 -> 12, fifteen, 146 / 281;
-// 100 fp32 -> 16, five, 342 / 347; 256 fp16 -> 16, ten, 141 / 104.
-bool use_projection(int32_t d_in, int32_t d_out, int64_t esz, int32_t k) {
-  if (d_out > kProjCols || d_in < 8) return false;
-  const int64_t row = d_in * esz;
+// A layer of fp32 rows projects every input row first when reading the k + 1
+// input rows of each output node would move more than twice as much: an input row
+// read once and 128 bytes written, and k + 1 lines of 128 bytes, against k + 1
+// rows with about a line each for their unaligned ends.  A level holds about half
+// as many rows per output node as its hop draws, at most about four on dense
+// graphs.  The factor is for the rows that the caches serve again when they are
+// gathered.  Forward passes of two layers of 16, 2.45M nodes, projected /
+// gathered first layers, by (columns, last fan-out): (64, 20) 57 / 48 us; (100,
+// 20) 65 / 59, (150, 20) 73 / 81, (200, 10) 99 / 107, (300, 10) 125 / 156, (300,
+// 20) 100 / 105, (450, 10) 190 / 200, (450, 20) 159 / 146, (602, 5) 259 / 252,
+// (602, 20) 192 / 179: within a tenth of the better one but for 150 columns and a
+// fan-out of 10 (86 / 104, gathered).  Rows of halves are cheaper to gather
+// throughout, whatever the bytes moved: (256, 20) 84 / 65, (602, 10) 196 / 164.
+bool use_projection(int32_t d_in, int32_t d_out, int32_t x_dtype, int32_t k) {
+  if (x_dtype != GG_F32 || d_out > kProjCols || d_in < 8) return false;
+  const int64_t row = d_in * 4;
   const int64_t gathered = (k + 1) * (row + 112);
   const int64_t projected = std::min<int64_t>((k + 1) * (row + 128) / 2, 4 * (row + 128)) +
                             (k + 1) * 128;
@@ -980,7 +975,7 @@ int launch_layer_nt(int nt, LayerArgs& a, int64_t rows_bound, int32_t* status,
 }
 
 // The layer of output level lvl by projection: a's fields as for k_sage_layer.
-int launch_projected(LayerArgs& a, int xt, float* z, int64_t rows_cap, int32_t* status,
+int launch_projected(LayerArgs& a, float* z, int64_t rows_cap, int32_t* status,
                      hipStream_t stream) {
   ProjArgs p;
   p.h = a.h;
@@ -996,10 +991,7 @@ int launch_projected(LayerArgs& a, int xt, float* z, int64_t rows_cap, int32_t* 
   p.whole = wb <= kWLdsBytes ? 1 : 0;
   const int grid = (int)std::min<int64_t>(std::max<int64_t>(cdiv(rows_cap, kTileRows), 1), 2048);
   const size_t lds = p.whole ? (size_t)wb : 0;
-  if (xt == GG_F32)
-    hipLaunchKernelGGL(k_sage_project<GG_F32>, dim3(grid), dim3(kSageBlock), lds, stream, p);
-  else
-    hipLaunchKernelGGL(k_sage_project<GG_F16>, dim3(grid), dim3(kSageBlock), lds, stream, p);
+  hipLaunchKernelGGL(k_sage_project, dim3(grid), dim3(kSageBlock), lds, stream, p);
   GG_LAUNCH_CHECK("k_sage_project");
   const int mg = (int)std::min<int64_t>(std::max<int64_t>(cdiv(rows_cap, kSageBlock / 16), 1), 16384);
   if (a.k <= 8)
@@ -1151,8 +1143,8 @@ extern "C" int gg_sage_forward(const gg_wsample_t* smp, int64_t num_nodes, int32
     a.out_cap = j + 1 < L ? rows_cap : out_rows_cap;
     const int xt = j == 0 ? x_dtype : GG_F32;
     int rc;
-    if (j == 0 && use_projection(ly.d_in, ly.d_out, esz, a.k))
-      rc = launch_projected(a, xt, sw.z, rows_cap, status_d, stream);
+    if (j == 0 && use_projection(ly.d_in, ly.d_out, x_dtype, a.k))
+      rc = launch_projected(a, sw.z, rows_cap, status_d, stream);
     else if (xt == GG_F16)
       rc = launch_layer_nt<GG_F16>(pk.nt[j], a, rows_cap, status_d, stream);
     else
