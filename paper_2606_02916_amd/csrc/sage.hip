@@ -505,14 +505,15 @@ __device__ __forceinline__ int anew(int v) {
 // 9.2e-8 with halves, 9.7e-8 projected).
 //
 // Wide rows are bound by the random row reads (262K x 602 fp32 -> 128, ten
-// neighbours, 77K outputs: 549 us for 2.1 GB of row reads, where projecting
+// neighbours, 77K outputs: 531 us for 2.1 GB of row reads, where projecting
 // every row by [W_self | W_neigh], whose 85 GFLOP the fp32 matrix cores need
 // 550 us for at best, took 2,447 + 119), narrow ones by matrix work (1.4M x
-// 128 fp16 -> 128, five neighbours: 234 us, 117 of them matrix cores at full
-// rate; projected 1,676 + 232).  Also measured on the first: the lookups of
-// k_sage_rows inside the tile loop and 64-byte runs 655; half the waves
-// gathering and half multiplying 858; 1 KB runs in two blocks per CU 594;
-// eight neighbour rows in flight instead of five, in two blocks per CU, 565.
+// 128 fp16 -> 128, five neighbours: 229 us, 117 of them matrix cores at full
+// rate; projected 1,676 + 232).  Also measured on the first, when it took 549:
+// the lookups of k_sage_rows inside the tile loop and 64-byte runs 655; half
+// the waves gathering and half multiplying 858; 1 KB runs in two blocks per CU
+// 594; eight neighbour rows in flight instead of five, in two blocks per CU,
+// 565.
 // Lane indices are taken anew in every tile (anew()): the addresses that the
 // compiler kept from tile to tile otherwise cost up to 50 registers and spilled.
 template <int NT, int XT, int LR, bool NARROW>
